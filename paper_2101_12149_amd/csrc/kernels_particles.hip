@@ -10,7 +10,7 @@
 //                     per-particle fields are never stored (Sec. 3.1).
 //  k_particles_global the same fused step without tiles (global memory and
 //                     global atomics, the paper's GPU deposition, Sec. 3.4.1)
-//  k_gather / k_push / k_deposit   the separate operations
+//  k_gather_box / k_push / k_deposit_box   the separate operations
 //  k_adjoint_push / k_adjoint_scatter_box (and their tiled forms)
 //                     transpose of the particle part of a step, two passes
 #include "pic_device.hpp"
@@ -1411,52 +1411,6 @@ __global__ void __launch_bounds__(256) k_particles_global(PConst<T> pc, PArr<T> 
     particle_step_global<T, O>(pc, sp, sp, fp, p, c, f, u, err);
 }
 
-template <typename T, int O>
-__global__ void __launch_bounds__(256) k_gather(PConst<T> pc, PArr<T> sp, FieldPtrs<T> fp, T *Ex, T *Ey, T *Ez,
-                                                T *Bx, T *By, T *Bz, int *err)
-{
-    constexpr int NW = Shape<O, T>::NW;
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= sp.n)
-        return;
-    int c[3];
-    T f[3];
-    T E[3] = {T(0), T(0), T(0)}, B[3] = {T(0), T(0), T(0)};
-    bool ok = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        c[d] = sp.cell[d][p];
-        f[d] = sp.off[d][p];
-        ok = ok && c[d] >= 0 && c[d] < pc.n[d] && f[d] >= T(0) && f[d] < T(1);
-    }
-    if (!ok)
-        atomicOr(err, 1);
-    if (ok) {
-        const int gs[3] = {1, pc.n[0], pc.n[0] * pc.n[1]};
-        AxisW<O, T> aw[3];
-        int on[3][NW], os[3][NW];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            axis_weights<O>(f[d], aw[d]);
-            axis_offsets_global<NW>(c[d], aw[d].bn, pc.n[d], gs[d], on[d]);
-            axis_offsets_global<NW>(c[d], aw[d].bs, pc.n[d], gs[d], os[d]);
-        }
-        FieldSrc<T> gf;
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-            gf.c[m] = fp.E[m];
-            gf.c[3 + m] = fp.B[m];
-        }
-        gather_eb<O>(gf, aw, on, os, E, B);
-    }
-    Ex[p] = E[0];
-    Ey[p] = E[1];
-    Ez[p] = E[2];
-    Bx[p] = B[0];
-    By[p] = B[1];
-    Bz[p] = B[2];
-}
-
 template <typename T>
 __global__ void __launch_bounds__(256) k_push(PConst<T> pc, PArr<T> sp, const T *Ex, const T *Ey, const T *Ez,
                                               const T *Bx, const T *By, const T *Bz, int *err)
@@ -1491,48 +1445,6 @@ __global__ void __launch_bounds__(256) k_push(PConst<T> pc, PArr<T> sp, const T 
         sp.off[d][p] = f1[d];
         sp.u[d][p] = u1[d];
     }
-}
-
-template <typename T, int O>
-__global__ void __launch_bounds__(256) k_deposit(PConst<T> pc, PArr<T> b, PArr<T> a, FieldPtrs<T> fp, int *err)
-{
-    constexpr int NW = Shape<O, T>::NW;
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= b.n)
-        return;
-    int c0[3], c1[3], kap[3];
-    T f0[3], f1[3], u[3];
-    if (!load_particle(b, p, pc.n, c0, f0, u, err))
-        return;
-    bool ok = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        c1[d] = a.cell[d][p];
-        f1[d] = a.off[d][p];
-        int k = c1[d] - c0[d];
-        if (k > pc.n[d] / 2)
-            k -= pc.n[d];
-        if (k < -(pc.n[d] / 2))
-            k += pc.n[d];
-        kap[d] = k;
-        ok = ok && k >= -1 && k <= 1 && c1[d] >= 0 && c1[d] < pc.n[d] && f1[d] >= T(0) && f1[d] < T(1);
-    }
-    if (!ok) {
-        atomicOr(err, 4);
-        return;
-    }
-    const T w = b.w ? b.w[p] : pc.w0;
-    const int gs[3] = {1, pc.n[0], pc.n[0] * pc.n[1]};
-    EskAxis<O, T> e[3];
-    T K[3];
-    int jo[3][NW + 1];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        esk_axis<O>(f0[d], f1[d], kap[d], e[d]);
-        K[d] = pc.jk[d] * w;
-        axis_offsets_global<NW + 1>(c0[d], e[d].lo, pc.n[d], gs[d], jo[d]);
-    }
-    esk_scatter<O, T, T>(e, jo, K, [&](int m, int idx, T v) { gatomic_add(fp.J[m] + idx, v); });
 }
 
 // ---------------------------------------------------------------------------
@@ -2103,6 +2015,399 @@ __device__ inline bool load_position(const PArr<T> &in, int64_t p, const int *n,
     return ok;
 }
 
+__device__ inline int wave_min(int v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+        v = min(v, __shfl_xor(v, o, 64));
+    return v;
+}
+
+__device__ inline int wave_max(int v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+        v = max(v, __shfl_xor(v, o, 64));
+    return v;
+}
+
+// cell offset from the reference cell along one axis, wrapped into [-n/2, n/2)
+__device__ inline int box_rel(int c, int ref, int n)
+{
+    int r = c - ref;
+    if (r < -(n >> 1))
+        r += n;
+    else if (r >= n - (n >> 1))
+        r -= n;
+    return r;
+}
+
+// ---------------------------------------------------------------------------
+// Separate gather and deposit on boxes.  A workgroup takes a run of
+// consecutive particles; when the cells of a segment of them (the run, or
+// after halving a part of it) fit a box whose region fits the LDS, the
+// fields of the box are staged there for the gather, or the current is
+// accumulated there in FP64 and flushed with one global atomic per non-zero
+// value.  Particles in any order are accepted: a segment of OPS_MIN
+// particles whose box does not fit runs on global memory.  There the deposit
+// is bound by its up to 300 global atomics per particle and the gather by
+// its 384 window reads through L1; in the LDS the deposit issues two atomics
+// per shared row and the gather reads at LDS rate.  2.1 M binned particles
+// (64^3, 8 per cell), FP32 order 3: deposit 4264 -> 186 us, gather 693 ->
+// 130 us.
+
+struct CellBox {
+    int ref[3];    // reference cell (in the grid)
+    int lo[3];     // first cell of the box relative to ref
+    int ext[3];    // cells per axis
+    bool any;      // a valid cell was seen
+    bool clumped;  // most neighbours in memory share a cell
+};
+
+constexpr int OPS_MIN = 512;        // smallest segment tried as a box
+constexpr int OPS_MAX_EXT = 480;    // cells per axis (the region walk takes rows of at most blockDim.x)
+constexpr int OPS_HEAD = 512;       // reduction scratch ahead of the regions, bytes
+static_assert((16 * 7 + 4) * (int)sizeof(int) <= OPS_HEAD, "box reduction scratch of 16 waves");
+
+// The box of the cells of particles [s0, s0 + seg) (particles with a cell
+// outside the grid are left out).  scratch: OPS_HEAD bytes of LDS.  The
+// result is the same in every thread; ends with a barrier.
+template <typename T>
+__device__ inline CellBox segment_box(const PArr<T> &sp, const int *n, int64_t s0, int seg, int *scratch)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
+    int(*wred)[7] = reinterpret_cast<int(*)[7]>(scratch);
+    CellBox b;
+    // reference: the segment's first particle, clamped into the grid
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int v = sp.cell[d][s0];
+        b.ref[d] = v < 0 ? 0 : (v >= n[d] ? n[d] - 1 : v);
+    }
+    int mn[3] = {INT_MAX, INT_MAX, INT_MAX}, mx[3] = {INT_MIN, INT_MIN, INT_MIN}, same = 0;
+    for (int j0 = 0; j0 < seg; j0 += blockDim.x) {
+        const int j = j0 + tid;
+        int c[3] = {-1, -1, -1};
+        if (j < seg) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                c[d] = sp.cell[d][s0 + j];
+        }
+        const bool ok = (c[0] >= 0) & (c[0] < n[0]) & (c[1] >= 0) & (c[1] < n[1]) & (c[2] >= 0) & (c[2] < n[2]);
+        if (ok) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const int r = box_rel(c[d], b.ref[d], n[d]);
+                mn[d] = min(mn[d], r);
+                mx[d] = max(mx[d], r);
+            }
+        }
+        bool eq = ok;
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+            eq = eq & (c[d] == __shfl_up(c[d], 1, 64));
+        same += eq && lane > 0 ? 1 : 0;
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        mn[d] = wave_min(mn[d]);
+        mx[d] = wave_max(mx[d]);
+    }
+    for (int o = 32; o > 0; o >>= 1)
+        same += __shfl_xor(same, o, 64);
+    if (lane == 0) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            wred[wv][d] = mn[d];
+            wred[wv][3 + d] = mx[d];
+        }
+        wred[wv][6] = same;
+    }
+    __syncthreads();
+    int tot = 0;
+    for (int w = 0; w < nw; ++w)
+        tot += wred[w][6];
+    b.any = true;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        int a = wred[0][d], e = wred[0][3 + d];
+        for (int w = 1; w < nw; ++w) {
+            a = min(a, wred[w][d]);
+            e = max(e, wred[w][3 + d]);
+        }
+        b.any = b.any && a <= e;
+        b.lo[d] = a;
+        b.ext[d] = b.any ? e - a + 1 : 0;
+    }
+    b.clumped = 2 * tot > seg;
+    __syncthreads();   // the scratch is free again
+    return b;
+}
+
+// region of a box with `halo` more nodes per axis; false where it does not
+// fit `room` values
+__device__ inline bool box_region(const CellBox &b, int halo, size_t room, int *ext)
+{
+    size_t vol = 1;
+    bool ok = true;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        ext[d] = b.ext[d] + halo;
+        ok = ok && b.ext[d] <= OPS_MAX_EXT;
+        vol *= (size_t)ext[d];
+    }
+    return ok && vol <= room;
+}
+
+// lane runs of a box: like xrun_key, for local positions up to OPS_MAX_EXT
+__device__ inline int xrun_key_box(const int *l)
+{
+    return (1 << 30) | (l[0] + 8) | ((l[1] + 8) << 10) | ((l[2] + 8) << 20);
+}
+
+// Threads of the box kernels: the LDS of a region of 14^3 nodes (a tile of
+// binned particles that drifted a cell) leaves one workgroup per CU, except
+// for the FP32 gather (66 KB), where two share it.
+template <typename T>
+struct OpsThreads {
+    static constexpr int gather = sizeof(T) == 4 ? 512 : 1024;
+    static constexpr int deposit = sizeof(T) == 4 ? 1024 : 512;
+    static constexpr size_t gather_lds = sizeof(T) == 4 ? 80 * 1024 : 160 * 1024;
+};
+
+template <typename T, int O>
+__global__ void __launch_bounds__(OpsThreads<T>::gather) k_gather_box(PConst<T> pc, PArr<T> sp, FieldPtrs<T> fp,
+                                                                     T *Ex, T *Ey, T *Ez, T *Bx, T *By, T *Bz,
+                                                                     int chunk, int room, int *err)
+{
+    constexpr int NW = Shape<O, T>::NW;
+    constexpr int lo = O == 3 ? 2 : 1;     // nodes below the box
+    constexpr int halo = O == 3 ? 4 : 2;   // on both sides together
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    T *sF = reinterpret_cast<T *>(smem_raw + OPS_HEAD);   // 6 * room values
+    const int64_t base = (int64_t)blockIdx.x * chunk;
+    const int64_t end = base + chunk < sp.n ? base + chunk : sp.n;
+    int len = chunk;
+    for (int64_t s0 = base; s0 < end;) {
+        const int seg = (int)(end - s0 < len ? end - s0 : len);
+        const CellBox b = segment_box(sp, pc.n, s0, seg, reinterpret_cast<int *>(smem_raw));
+        int ext[3];
+        const bool fits = b.any && box_region(b, halo, (size_t)room, ext);
+        if (b.any && !fits && len > OPS_MIN) {
+            len >>= 1;   // uniform: every thread has the same box
+            continue;
+        }
+        const int vol = fits ? ext[0] * ext[1] * ext[2] : 0;
+        const int sf[3] = {1, ext[0], ext[0] * ext[1]};
+        if (fits) {
+            const int org[3] = {b.ref[0] + b.lo[0], b.ref[1] + b.lo[1], b.ref[2] + b.lo[2]};
+            region_walk(pc.n, org, lo, ext[0], ext[1], ext[2], ext[0], false, [&](int r, int gi) {
+                T v[6];
+#pragma unroll
+                for (int m = 0; m < 3; ++m) {
+                    v[m] = fp.E[m][gi];
+                    v[3 + m] = fp.B[m][gi];
+                }
+#pragma unroll
+                for (int m = 0; m < 6; ++m)
+                    sF[m * vol + r] = v[m];
+            });
+            __syncthreads();
+        }
+        for (int j = threadIdx.x; j < seg; j += blockDim.x) {
+            const int64_t p = s0 + j;
+            int c[3];
+            T f[3];
+            T E[3] = {T(0), T(0), T(0)}, B[3] = {T(0), T(0), T(0)};
+            if (!load_position(sp, p, pc.n, c, f)) {
+                atomicOr(err, 1);
+            } else {
+                const int gs[3] = {1, pc.n[0], pc.n[0] * pc.n[1]};
+                AxisW<O, T> aw[3];
+                int on[3][NW], os[3][NW];
+                FieldSrc<T> src;
+                if (fits) {
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        const int l = box_rel(c[d], b.ref[d], pc.n[d]) - b.lo[d] + lo;
+                        axis_weights<O>(f[d], aw[d]);
+                        axis_offsets_local<NW>(l, aw[d].bn, sf[d], on[d]);
+                        axis_offsets_local<NW>(l, aw[d].bs, sf[d], os[d]);
+                    }
+#pragma unroll
+                    for (int m = 0; m < 6; ++m)
+                        src.c[m] = sF + m * vol;
+                    gather_eb<O>(src, aw, on, os, E, B);
+                } else {
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        axis_weights<O>(f[d], aw[d]);
+                        axis_offsets_global<NW>(c[d], aw[d].bn, pc.n[d], gs[d], on[d]);
+                        axis_offsets_global<NW>(c[d], aw[d].bs, pc.n[d], gs[d], os[d]);
+                    }
+                    src = global_fields(fp);
+                    gather_eb<O>(src, aw, on, os, E, B);
+                }
+            }
+            Ex[p] = E[0];
+            Ey[p] = E[1];
+            Ez[p] = E[2];
+            Bx[p] = B[0];
+            By[p] = B[1];
+            Bz[p] = B[2];
+        }
+        __syncthreads();   // the next segment stages into the same region
+        s0 += seg;
+    }
+}
+
+// Positions before and after of particle p with the checks of the deposit:
+// flags the error word and returns false for corrupt state or a move of more
+// than a cell.
+template <typename T>
+__device__ inline bool load_move(const PArr<T> &b, const PArr<T> &a, int64_t p, const int *n, int *c0, T *f0, T *f1,
+                                 int *kap, int *err)
+{
+    int c1[3];
+    T u[3];
+    load_state(b, p, c0, f0, u);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        c1[d] = a.cell[d][p];
+        f1[d] = a.off[d][p];
+    }
+    if (!check_state(n, c0, f0, u, err))
+        return false;
+    bool ok = true;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        int k = c1[d] - c0[d];
+        if (k > n[d] / 2)
+            k -= n[d];
+        if (k < -(n[d] / 2))
+            k += n[d];
+        kap[d] = k;
+        ok = ok & (k >= -1) & (k <= 1) & (c1[d] >= 0) & (c1[d] < n[d]) & (f1[d] >= T(0)) & (f1[d] < T(1));
+    }
+    if (!ok)
+        atomicOr(err, 4);
+    return ok;
+}
+
+// The particles that stay in their cells share rows along lane runs where
+// consecutive particles sit in consecutive cells (the sort's order); those
+// that change cells are listed and deposited afterwards in full waves, one
+// lane per particle and component.  Where consecutive particles share a cell
+// (a load listed cell by cell) the lanes of a wave take particles seg /
+// blockDim.x apart, so that their atomics go to distinct addresses.
+template <typename T, int O>
+__global__ void __launch_bounds__(OpsThreads<T>::deposit) k_deposit_box(PConst<T> pc, PArr<T> b, PArr<T> a,
+                                                                       FieldPtrs<T> fp, int chunk, int room, int *err)
+{
+    constexpr int NW = Shape<O, T>::NW;
+    constexpr int lo = O == 3 ? 2 : 1;     // nodes below the box
+    constexpr int halo = O == 3 ? 5 : 3;   // on both sides together
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    int *qcnt = reinterpret_cast<int *>(smem_raw) + 16 * 7;
+    double *sJ = reinterpret_cast<double *>(smem_raw + OPS_HEAD);             // 3 * room values
+    unsigned short *qj = reinterpret_cast<unsigned short *>(sJ + 3 * room);   // chunk entries
+    const int tid = threadIdx.x, nth = blockDim.x;
+    const int64_t base = (int64_t)blockIdx.x * chunk;
+    const int64_t end = base + chunk < b.n ? base + chunk : b.n;
+    int len = chunk;
+    for (int64_t s0 = base; s0 < end;) {
+        const int seg = (int)(end - s0 < len ? end - s0 : len);
+        const CellBox bx = segment_box(b, pc.n, s0, seg, reinterpret_cast<int *>(smem_raw));
+        int ext[3];
+        const bool fits = bx.any && box_region(bx, halo, (size_t)room, ext);
+        if (bx.any && !fits && len > OPS_MIN) {
+            len >>= 1;   // uniform
+            continue;
+        }
+        if (!fits) {
+            for (int j = tid; j < seg; j += nth) {
+                int c0[3], kap[3];
+                T f0[3], f1[3];
+                if (load_move(b, a, s0 + j, pc.n, c0, f0, f1, kap, err))
+                    deposit_global_full<T, O>(pc, fp, c0, f0, f1, kap, b.w ? b.w[s0 + j] : pc.w0);
+            }
+            s0 += seg;
+            continue;
+        }
+        const int vol = ext[0] * ext[1] * ext[2];
+        const int sj[3] = {1, ext[0], ext[0] * ext[1]};
+        for (int r = tid; r < 3 * vol; r += nth)
+            sJ[r] = 0.0;
+        if (tid == 0)
+            *qcnt = 0;
+        __syncthreads();
+        const int per = (seg + nth - 1) / nth;
+        for (int k = 0; k < per; ++k) {
+            const int j = bx.clumped ? tid * per + k : k * nth + tid;
+            int key = 0;
+            int c0[3], kap[3], l[3] = {0, 0, 0};
+            T f0[3] = {T(0), T(0), T(0)}, f1[3] = {T(0), T(0), T(0)}, w = T(0);
+            bool crosser = false;
+            if (j < seg && load_move(b, a, s0 + j, pc.n, c0, f0, f1, kap, err)) {
+                if ((kap[0] | kap[1] | kap[2]) == 0) {
+                    w = b.w ? b.w[s0 + j] : pc.w0;
+#pragma unroll
+                    for (int d = 0; d < 3; ++d)
+                        l[d] = box_rel(c0[d], bx.ref[d], pc.n[d]) - bx.lo[d];
+                    key = xrun_key_box(l);
+                } else {
+                    crosser = true;
+                }
+            }
+            // the wave is converged here
+            const unsigned long long m = __ballot(crosser);
+            if (m != 0) {   // uniform across the wave
+                const int lane = tid & 63, leader = __ffsll((long long)m) - 1;
+                int at = 0;
+                if (lane == leader)
+                    at = atomicAdd(qcnt, __popcll(m));
+                at = __shfl(at, leader);
+                if (crosser)
+                    qj[at + __popcll(m & ((1ull << lane) - 1ull))] = (unsigned short)j;
+            }
+            const XRun xr = xrun(key);
+            if (key != 0)
+                deposit_still_shared<T, O>(pc, f0, f1, l, lo, sj, w, sJ, vol, xr);
+        }
+        __syncthreads();
+        const int nq = *qcnt;
+        for (int i = tid; i < 3 * nq; i += nth) {
+            const int m = i / nq;
+            const int64_t p = s0 + qj[i - m * nq];
+            int c0[3], kap[3], l[3];
+            T f0[3], f1[3];
+            load_move(b, a, p, pc.n, c0, f0, f1, kap, err);   // checked above
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                l[d] = box_rel(c0[d], bx.ref[d], pc.n[d]) - bx.lo[d];
+            const T w = b.w ? b.w[p] : pc.w0;
+            if (m == 0)
+                deposit_local_full<T, O, 0>(pc, f0, f1, kap, l, lo, sj, w, sJ, vol);
+            else if (m == 1)
+                deposit_local_full<T, O, 1>(pc, f0, f1, kap, l, lo, sj, w, sJ, vol);
+            else
+                deposit_local_full<T, O, 2>(pc, f0, f1, kap, l, lo, sj, w, sJ, vol);
+        }
+        __syncthreads();
+        const int org[3] = {bx.ref[0] + bx.lo[0], bx.ref[1] + bx.lo[1], bx.ref[2] + bx.lo[2]};
+        region_walk(pc.n, org, lo, ext[0], ext[1], ext[2], ext[0], false, [&](int r, int gi) {
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+                const T v = (T)sJ[m * vol + r];
+                if (v != T(0))
+                    gatomic_add(fp.J[m] + gi, v);
+            }
+        });
+        __syncthreads();   // the next segment clears the accumulators
+        s0 += seg;
+    }
+}
+
 template <typename T, int O>
 // (at least two waves per SIMD: the FP64 order-3 pass sits at the 256
 // registers that allow two, and one register more would halve them)
@@ -2143,33 +2448,6 @@ constexpr int BOX_HEAD = 256;   // reduction scratch ahead of the accumulators
 constexpr int BOX_MAX_CELLS = 40;   // box extent per axis (lane-run keys hold local coordinates below 56)
 static_assert((6 * (BOX_THREADS / 64) + 3) * (int)sizeof(int) <= BOX_HEAD, "box reduction scratch");
 static_assert(BOX_HEAD + BOX_LDS <= 160 * 1024, "box scatter LDS");
-
-__device__ inline int wave_min(int v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-        v = min(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
-__device__ inline int wave_max(int v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-        v = max(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
-// cell offset from the reference cell along one axis, wrapped into [-n/2, n/2)
-__device__ inline int box_rel(int c, int ref, int n)
-{
-    int r = c - ref;
-    if (r < -(n >> 1))
-        r += n;
-    else if (r >= n - (n >> 1))
-        r -= n;
-    return r;
-}
 
 template <typename T, int O>
 __global__ void __launch_bounds__(BOX_THREADS) k_adjoint_scatter_box(PConst<T> pc, PArr<T> sp, AdjPtrs<T> ap,
@@ -2917,19 +3195,39 @@ hipError_t launch_particles_global(int order, const PConst<T> &pc, const PArr<T>
     return hipGetLastError();
 }
 
+// consecutive particles per workgroup of the box kernels: a tile's worth at
+// 8 per cell, less on a small species so that there are two workgroups per
+// CU (not below OPS_MIN)
+static int ops_chunk(int64_t n)
+{
+    int c = 4096;
+    while (c > OPS_MIN && n < (int64_t)c * 512)
+        c >>= 1;
+    return c;
+}
+
+template <typename T, int O>
+static hipError_t launch_gather_o(const PConst<T> &pc, const PArr<T> &sp, const FieldPtrs<T> &f, T *const Ep[3],
+                                  T *const Bp[3], int *err, hipStream_t st)
+{
+    static bool attr = false;
+    allow_big_lds(&k_gather_box<T, O>, attr);
+    const int chunk = ops_chunk(sp.n);
+    const size_t lds = OpsThreads<T>::gather_lds;
+    const int room = (int)((lds - OPS_HEAD) / (6 * sizeof(T)));
+    hipLaunchKernelGGL((k_gather_box<T, O>), dim3(nblk(sp.n, chunk)), dim3(OpsThreads<T>::gather), lds, st, pc, sp, f,
+                       Ep[0], Ep[1], Ep[2], Bp[0], Bp[1], Bp[2], chunk, room, err);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_gather(int order, const PConst<T> &pc, const PArr<T> &sp, const FieldPtrs<T> &f, T *const Ep[3],
                          T *const Bp[3], int *err, hipStream_t st)
 {
     if (sp.n == 0)
         return hipSuccess;
-    if (order == 1)
-        hipLaunchKernelGGL((k_gather<T, 1>), dim3(nblk(sp.n, 256)), dim3(256), 0, st, pc, sp, f, Ep[0], Ep[1],
-                           Ep[2], Bp[0], Bp[1], Bp[2], err);
-    else
-        hipLaunchKernelGGL((k_gather<T, 3>), dim3(nblk(sp.n, 256)), dim3(256), 0, st, pc, sp, f, Ep[0], Ep[1],
-                           Ep[2], Bp[0], Bp[1], Bp[2], err);
-    return hipGetLastError();
+    return order == 1 ? launch_gather_o<T, 1>(pc, sp, f, Ep, Bp, err, st)
+                      : launch_gather_o<T, 3>(pc, sp, f, Ep, Bp, err, st);
 }
 
 template <typename T>
@@ -2943,19 +3241,28 @@ hipError_t launch_push(const PConst<T> &pc, const PArr<T> &sp, T *const Ep[3], T
     return hipGetLastError();
 }
 
+template <typename T, int O>
+static hipError_t launch_deposit_o(const PConst<T> &pc, const PArr<T> &before, const PArr<T> &after,
+                                   const FieldPtrs<T> &f, int *err, hipStream_t st)
+{
+    static bool attr = false;
+    allow_big_lds(&k_deposit_box<T, O>, attr);
+    const int chunk = ops_chunk(before.n);
+    const size_t lds = 160 * 1024;
+    const int room = (int)((lds - OPS_HEAD - 2 * (size_t)chunk) / (3 * sizeof(double)));
+    hipLaunchKernelGGL((k_deposit_box<T, O>), dim3(nblk(before.n, chunk)), dim3(OpsThreads<T>::deposit), lds, st, pc,
+                       before, after, f, chunk, room, err);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_deposit(int order, const PConst<T> &pc, const PArr<T> &before, const PArr<T> &after,
                           const FieldPtrs<T> &f, int *err, hipStream_t st)
 {
     if (before.n == 0)
         return hipSuccess;
-    if (order == 1)
-        hipLaunchKernelGGL((k_deposit<T, 1>), dim3(nblk(before.n, 256)), dim3(256), 0, st, pc, before, after, f,
-                           err);
-    else
-        hipLaunchKernelGGL((k_deposit<T, 3>), dim3(nblk(before.n, 256)), dim3(256), 0, st, pc, before, after, f,
-                           err);
-    return hipGetLastError();
+    return order == 1 ? launch_deposit_o<T, 1>(pc, before, after, f, err, st)
+                      : launch_deposit_o<T, 3>(pc, before, after, f, err, st);
 }
 
 template <typename T>

@@ -193,6 +193,49 @@ def test_deposit_matches_oracle_and_conserves_charge(order, dtype):
     assert np.linalg.norm(drho + divJ) / np.linalg.norm(drho) < (1e-13 if dtype == "f64" else 1e-6)
 
 
+@pytest.mark.parametrize("layout", ["rank_major", "cell_by_cell", "scattered", "corner_then_far"])
+@pytest.mark.parametrize("order", [1, 3])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_separate_gather_and_deposit_on_boxes_match_oracle(order, dtype, layout):
+    """The separate gather and deposit stage a run of consecutive particles in
+    an LDS box of their cells: the order of a sort (lanes in neighbouring
+    cells), a load listed cell by cell (lanes in one cell), particles anywhere
+    in a grid whose box does not fit (global memory), and a run that holds a
+    block across the periodic corner and a distant one (halved).  The count
+    leaves a partial run, and a twentieth of the particles cross a face."""
+    g = wl.plasma_grid((24, 40, 32), order)
+    n, gen = 5003, torch.Generator().manual_seed(71)
+    if layout == "scattered":
+        cells = torch.stack([torch.randint(0, int(g.n[d]), (n,), generator=gen) for d in range(3)]).to(torch.int32)
+    elif layout == "corner_then_far":
+        a = torch.randint(0, 6, (3, n), generator=gen) + torch.tensor([[21], [37], [29]])
+        b = torch.randint(0, 4, (3, n), generator=gen) + torch.tensor([[10], [15], [12]])
+        k = torch.arange(n)[None]
+        cells = (torch.where((k >= 1536) & (k < 2304), b, a) % torch.tensor(g.n)[:, None]).to(torch.int32)
+    else:
+        ppc = 8
+        cell = torch.arange(n // ppc + 1).repeat_interleave(ppc) if layout == "cell_by_cell" else \
+            torch.cat([torch.arange(t, min(t + 512, n // ppc + 1)).repeat(ppc) for t in range(0, n // ppc + 1, 512)])
+        cell = cell[:n]
+        cells = torch.stack([cell % 8 + 3, (cell // 8) % 8 + 36, cell // 64 + 28])
+        cells = (cells % torch.tensor(g.n)[:, None]).to(torch.int32)
+    before = random_species(g, n, 72, dtype=dtype, cells=cells)
+    after = _displaced(g, before, 73, amp=0.05)
+    f = random_fields(g, 74, dtype=dtype)
+    Ep, Bp = _lib.pic_gather(g, dev(before), dev(f))
+    df = dev(f)
+    df.J.fill_(0.25)   # the deposit adds to what is there
+    _lib.pic_deposit(g, dev(before), dev(after), df)
+    torch.cuda.synchronize()
+    oE, oB = oracle.gather(g, before.numpy(), f.numpy())
+    of = f.numpy()
+    of.J[:] = 0.25
+    oracle.deposit(g, before.numpy(), after.numpy(), of)
+    assert max_rel(_cpu(Ep), oE) < (F64_TOL if dtype == "f64" else 2e-6)
+    assert max_rel(_cpu(Bp), oB) < (F64_TOL if dtype == "f64" else 2e-6)
+    assert rel_l2(_cpu(df.J), of.J) < (F64_TOL if dtype == "f64" else 1e-5)
+
+
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 def test_yee_matches_oracle_with_source(dtype):
     g = _grid((16, 12, 20))
