@@ -33,10 +33,10 @@ VALU_PEAK_TFLOPS = 78.6
 # 6 x 14 FMA = 168, Boris 68, position 28, Esirkepov shapes 12, products and
 # sums 126
 FLOPS_PER_PARTICLE = {3: 2028, 1: 411}
-# calibrated HBM bytes per launch of the FP32 two-phase tile kernel at
-# 256^3 / 8 ppc, from the FETCH_SIZE / WRITE_SIZE passes (scaled by a 1 GiB
-# copy); only figures taken on the current kernel are listed
-MEASURED_TRAFFIC = {"uniform256_o3_f32": 17.49e9}
+# calibrated HBM bytes per launch of the fused tile kernel of a workload, from
+# the FETCH_SIZE / WRITE_SIZE passes (scaled by a 1 GiB copy); only figures
+# taken on the current kernel are listed
+MEASURED_TRAFFIC = {}
 
 
 def log(*a):
@@ -125,9 +125,9 @@ def run_adjoint(w, nrep, tile_start):
 
 
 def tile_kernel_name(npart, ncell, tsize, order):
-    """The fused particle kernel the library runs: the two-phase one for
-    FP32 order 3 at 6 or more particles per cell, else the one-pass one."""
-    return "k_particles_cells" if tsize == 4 and order == 3 and npart >= 6 * ncell else "k_particles_tile"
+    """The fused particle kernel the library runs with its automatic tiles:
+    on the matrix cores for FP32 order 3, else the one-pass one."""
+    return "k_particles_quads" if tsize == 4 and order == 3 else "k_particles_tile"
 
 
 def kernel_roofs(kernels, npart, ncell, tsize, has_w, order):

@@ -14,7 +14,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpic355.so")
-SOURCES = ["kernels_particles.hip", "kernels_grid.hip", "capi.hip"]
+SOURCES = ["kernels_particles.hip", "kernels_quads.hip", "kernels_grid.hip", "capi.hip"]
 MICRO_SRC = "microbench.hip"
 MICRO_LIB = os.path.join(HERE, "libpic355_micro.so")
 ARCH = os.environ.get("PIC355_ARCH", "gfx950")

@@ -13,10 +13,14 @@
 //  k_gather_box / k_push / k_deposit_box   the separate operations
 //  k_adjoint_push / k_adjoint_scatter_box (and their tiled forms)
 //                     transpose of the particle part of a step, two passes
-#include "pic_device.hpp"
-#include "pic_types.hpp"
+#include "particle_common.hpp"
 
 namespace pic {
+
+// threads per workgroup of the stray kernels: the particles outside their
+// tile's regions (they drifted since the binning), listed by the tile
+// kernels, so that they run in full waves
+constexpr int STRAY_THREADS = 256;
 
 // threads per tile workgroup: at 8 particles per cell and 8^3-cell tiles each
 // thread takes about one cell's particles, so neighbouring lanes touch
@@ -27,309 +31,6 @@ constexpr int TILE_THREADS = 512;
 template <typename T>
 struct TileThreads {
     static constexpr int value = sizeof(T) == 4 ? 1024 : 512;
-};
-
-template <typename T>
-__device__ inline void gatomic_add(T *p, T v)
-{
-    unsafeAtomicAdd(p, v);
-}
-
-template <typename T>
-__device__ inline void latomic_add(T *p, T v)
-{
-    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-__device__ inline int wrap_once(int v, int n)
-{
-    return v < 0 ? v + n : (v >= n ? v - n : v);
-}
-
-__device__ inline int wrap_any(int v, int n)
-{
-    int r = v % n;
-    return r < 0 ? r + n : r;
-}
-
-// momentum update of the push: Boris or Vay (uniform across the launch)
-template <typename T>
-__device__ inline void push_momentum(const PConst<T> &pc, const T *u, const T *E, const T *B, T *u1)
-{
-    if (pc.vay) {
-        vay(pc.h, pc.inv_c2, u, E, B, u1);
-    } else {
-        BorisTape<T> tp;
-        boris(pc.h, pc.inv_c2, u, E, B, u1, tp);
-    }
-}
-
-template <typename T>
-__device__ inline bool finite3(const T *u)
-{
-    return isfinite(u[0]) & isfinite(u[1]) & isfinite(u[2]);
-}
-
-// Load a particle and check its state; returns false (and flags err) for a
-// cell outside [0,n), an offset outside [0,1) or a non-finite momentum.
-// the state words of particle p, unchecked
-template <typename T>
-__device__ __attribute__((always_inline)) inline void load_state(const PArr<T> &in, int64_t p, int *c, T *f, T *u)
-{
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        c[d] = in.cell[d][p];
-        f[d] = in.off[d][p];
-        u[d] = in.u[d][p];
-    }
-}
-
-// true for a valid state (cell in the grid, offsets in [0,1), finite
-// momentum); an invalid one sets bit 0 of the error word
-template <typename T>
-__device__ inline bool check_state(const int *n, const int *c, const T *f, const T *u, int *err)
-{
-    // no short-circuit branches: a branch between the loads of load_state
-    // and their uses lets the compiler move later loads behind earlier checks
-    bool ok = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-        ok = ok & (c[d] >= 0) & (c[d] < n[d]) & (f[d] >= T(0)) & (f[d] < T(1));
-    ok = ok & finite3(u);
-    if (!ok)
-        atomicOr(err, 1);
-    return ok;
-}
-
-template <typename T>
-__device__ inline bool load_particle(const PArr<T> &in, int64_t p, const int *n, int *c, T *f, T *u, int *err)
-{
-    load_state(in, p, c, f, u);
-    return check_state(n, c, f, u, err);
-}
-
-template <typename T>
-__device__ inline void copy_particle(const PArr<T> &in, const PArr<T> &out, int64_t p)
-{
-    if (in.cell[0] == out.cell[0])
-        return;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        out.cell[d][p] = in.cell[d][p];
-        out.off[d][p] = in.off[d][p];
-        out.u[d][p] = in.u[d][p];
-    }
-    if (out.w)
-        out.w[p] = in.w[p];
-}
-
-// ---------------------------------------------------------------------------
-// tiles
-
-template <typename T>
-__device__ inline FieldSrc<T> global_fields(const FieldPtrs<T> &fp)
-{
-    FieldSrc<T> gf;
-#pragma unroll
-    for (int m = 0; m < 3; ++m) {
-        gf.c[m] = fp.E[m];
-        gf.c[3 + m] = fp.B[m];
-    }
-    return gf;
-}
-
-struct TileSpan {
-    int t;       // logical tile index (x fastest)
-    int t0[3];
-    int64_t ps, pe;
-};
-
-__device__ inline TileSpan tile_span(const TileGeo &tg, const int *tile_start, int64_t N)
-{
-    const int ntiles = tg.nt[0] * tg.nt[1] * tg.nt[2];
-    int t = blockIdx.x;
-    if (tg.xcd_map)
-        t = (t & 7) * (ntiles >> 3) + (t >> 3);
-    TileSpan s;
-    s.t = t;
-    s.t0[0] = (t % tg.nt[0]) * tg.t[0];
-    s.t0[1] = ((t / tg.nt[0]) % tg.nt[1]) * tg.t[1];
-    s.t0[2] = (t / (tg.nt[0] * tg.nt[1])) * tg.t[2];
-    int64_t ps = tile_start[t], pe = tile_start[t + 1];
-    ps = ps < 0 ? 0 : (ps > N ? N : ps);
-    pe = pe < ps ? ps : (pe > N ? N : pe);
-    s.ps = ps;
-    s.pe = pe;
-    return s;
-}
-
-// cell position relative to the tile origin, periodic; true when inside
-__device__ inline bool tile_local(const TileGeo &tg, const int *n, const int *t0, const int *c, int *l)
-{
-    bool inside = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        int v = c[d] - t0[d];
-        if (v < -tg.slack)
-            v += n[d];
-        else if (v >= tg.t[d] + tg.slack)
-            v -= n[d];
-        l[d] = v;
-        inside = inside && v >= -tg.slack && v < tg.t[d] + tg.slack;
-    }
-    return inside;
-}
-
-// logical tile of a cell, and the first cell of a tile
-__device__ __attribute__((always_inline)) inline int cell_tile(const TileGeo &tg, const int *c)
-{
-    return c[0] / tg.t[0] + tg.nt[0] * (c[1] / tg.t[1] + tg.nt[1] * (c[2] / tg.t[2]));
-}
-
-__device__ __attribute__((always_inline)) inline void tile_origin(const TileGeo &tg, int t, int *t0)
-{
-    t0[0] = (t % tg.nt[0]) * tg.t[0];
-    t0[1] = ((t / tg.nt[0]) % tg.nt[1]) * tg.t[1];
-    t0[2] = (t / (tg.nt[0] * tg.nt[1])) * tg.t[2];
-}
-
-// Status of a moved particle for the next step: 0 if its new cell c1 is in
-// its home tile's region (or no list slot is free, which leaves it to the
-// stray kernel), 1 once it is listed as a guest of the tile holding c1.
-__device__ __attribute__((always_inline)) inline unsigned char guest_next(const GuestArgs &g, const TileGeo &tg, const int *n, int64_t p, int home,
-                                           const int *home_t0, const int *c1)
-{
-    int l[3];
-    if (tile_local(tg, n, home_t0, c1, l) || p > 0x7fffffff)
-        return 0;
-    const int host = cell_tile(tg, c1);
-    const int slot = atomicAdd(g.cnt_next + host, 1);
-    if (slot >= g.cap)
-        return 0;
-    g.list_next[(int64_t)host * g.cap + slot] = make_int2((int)p, home);
-    return 1;
-}
-
-// Walk of a tile region (ex x ey x ez cells from t0 - lo, x fastest, LDS row
-// pitch px >= ex) by the whole workgroup without integer divisions in the
-// loop: a thread keeps one x (its position in a group of LX lanes, LX the
-// power of two >= ex) and steps over the rows (y, z) by blockDim.x / LX,
-// carrying y into z.  fn(local index, global index) runs once per cell.
-// With once, every axis of the region wraps at most once around the grid
-// (see region_wraps_once), else each row takes the general wrap.
-template <typename Fn>
-__device__ __attribute__((always_inline)) inline void region_walk(const int *n, const int *t0, int lo, int ex,
-                                                                   int ey, int ez, int px, bool once, Fn &&fn)
-{
-    const int lb = ex > 1 ? 32 - __clz(ex - 1) : 0;
-    const int x = (int)threadIdx.x & ((1 << lb) - 1);
-    const int step = (int)blockDim.x >> lb;   // >= 1: regions are at most 64 cells wide
-    if (x >= ex || step == 0)
-        return;
-    int row = (int)threadIdx.x >> lb;
-    int y = row % ey, z = row / ey;
-    const int sy = step % ey, sz = step / ey;
-    const int gx = wrap_any(t0[0] - lo + x, n[0]);
-    const int nrow = ey * ez;
-    for (; row < nrow; row += step) {
-        const int vy = t0[1] - lo + y, vz = t0[2] - lo + z;
-        const int gy = once ? wrap_once(vy, n[1]) : wrap_any(vy, n[1]);
-        const int gz = once ? wrap_once(vz, n[2]) : wrap_any(vz, n[2]);
-        fn(x + px * (y + ey * z), gx + n[0] * (gy + n[1] * gz));
-        y += sy;
-        z += sz;
-        if (y >= ey) {
-            y -= ey;
-            ++z;
-        }
-    }
-}
-
-// true when the region of extents e starting lo cells below a tile of
-// extents t wraps each axis of the grid at most once (wrap_once suffices)
-__device__ inline bool region_wraps_once(const int *n, const int *t, int lo, const int *e)
-{
-    bool ok = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-        ok = ok && lo <= n[d] && e[d] - t[d] - lo <= n[d];
-    return ok;
-}
-
-// Particles of a tile whose cell lies outside the tile's regions (they
-// drifted since the binning) are left out by the tile kernels and taken by
-// the stray kernels below, which first gather a chunk's strays into an LDS
-// list so that they run in full waves rather than as a few divergent lanes
-// of every wave.
-constexpr int STRAY_THREADS = 256;
-constexpr int STRAY_CHUNK = 4096;
-
-// Collect the in-tile indices j in [j0, j0 + STRAY_CHUNK) for which
-// is_stray(p) holds into the LDS list; returns the count.
-template <typename Pred>
-__device__ inline int collect_strays(const TileSpan &ts, int j0, int *list, int *cnt, Pred &&is_stray)
-{
-    if (threadIdx.x == 0)
-        *cnt = 0;
-    __syncthreads();
-    const int np = (int)(ts.pe - ts.ps);
-    const int je = np < j0 + STRAY_CHUNK ? np : j0 + STRAY_CHUNK;
-    for (int j = j0 + (int)threadIdx.x; j < je; j += blockDim.x)
-        if (is_stray(ts.ps + j))
-            list[atomicAdd(cnt, 1)] = j;
-    __syncthreads();
-    const int k = *cnt;
-    __syncthreads();   // every thread has the count before the next reset
-    return k;
-}
-
-// A list of strays on the device, appended to by the tile kernels (one
-// atomic per wave) and worked through by the stray kernels; cnt is cleared
-// before the tile kernel runs.  cap >= the particle count.
-struct StrayList {
-    int *p;
-    int *cnt;
-    int cap;
-};
-
-// appends p for every lane with `want`; call with the whole wave converged
-__device__ inline void stray_append(bool want, int p, const StrayList &sl)
-{
-    const int lane = threadIdx.x & 63;
-    const unsigned long long m = __ballot(want);
-    if (m == 0)
-        return;   // uniform across the wave
-    const int leader = __ffsll((long long)m) - 1;
-    int base = 0;
-    if (lane == leader)
-        base = atomicAdd(sl.cnt, __popcll(m));
-    base = __shfl(base, leader);
-    if (want) {
-        const int i = base + __popcll(m & ((1ull << lane) - 1ull));
-        if (i < sl.cap)
-            sl.p[i] = p;
-    }
-}
-
-// stray test from the cell (for kernels that do not move particles); an
-// invalid cell is not a stray, the tile kernel flags it
-template <typename T>
-struct CellStray {
-    const TileGeo &tg;
-    const int *n;
-    const TileSpan &ts;
-    const PArr<T> &sp;
-    __device__ bool operator()(int64_t p) const
-    {
-        int c[3], l[3];
-        bool ok = true;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            c[d] = sp.cell[d][p];
-            ok = ok && c[d] >= 0 && c[d] < n[d];
-        }
-        return ok && !tile_local(tg, n, ts.t0, c, l);
-    }
 };
 
 // ---------------------------------------------------------------------------
@@ -1054,47 +755,6 @@ struct StillRows {
         }
     }
 };
-
-// Esirkepov full-window current of component M into the component's LDS
-// accumulator
-template <typename T, int O, int M>
-__device__ __attribute__((always_inline)) inline void deposit_local_comp(const PConst<T> &pc, const T *f0, const T *f1,
-                                                                         const int *kap, const int *l, int lo_j,
-                                                                         const int *sj, T w, double *sA)
-{
-    constexpr int NW = Shape<O, T>::NW;
-    EskAxis<O, T> e[3];
-    T K[3];
-    int jo[3][NW + 1];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        esk_axis<O>(f0[d], f1[d], kap[d], e[d]);
-        K[d] = pc.jk[d] * w;
-        axis_offsets_local<NW + 1>(l[d] + lo_j, e[d].lo, sj[d], jo[d]);
-    }
-    esk_scatter<O, T, double, M>(e, jo, K, [&](int, int idx, double v) { latomic_add(sA + idx, v); });
-}
-
-// Esirkepov full-window current straight into global memory (a crosser
-// that found the queue full)
-template <typename T, int O>
-__device__ __attribute__((always_inline)) inline void deposit_global_full(const PConst<T> &pc, const FieldPtrs<T> &fp,
-                                                                          const int *c, const T *f0, const T *f1,
-                                                                          const int *kap, T w)
-{
-    constexpr int NW = Shape<O, T>::NW;
-    const int gs[3] = {1, pc.n[0], pc.n[0] * pc.n[1]};
-    EskAxis<O, T> e[3];
-    T K[3];
-    int jo[3][NW + 1];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        esk_axis<O>(f0[d], f1[d], kap[d], e[d]);
-        K[d] = pc.jk[d] * w;
-        axis_offsets_global<NW + 1>(c[d], e[d].lo, pc.n[d], gs[d], jo[d]);
-    }
-    esk_scatter<O, T, T>(e, jo, K, [&](int m, int idx, T v) { gatomic_add(fp.J[m] + idx, v); });
-}
 
 // Phase B for component M: the per-cell sums of the listed still particles,
 // the still particles of the slack cells, the queued crossers; `last`
@@ -3102,14 +2762,17 @@ static hipError_t launch_tile_o(const PConst<T> &pc, const TileGeo &tg, const PA
 {
     static bool attr_plain = false, attr_guests = false, attr_cp = false, attr_cg = false;
     const unsigned ntiles = (unsigned)(tg.nt[0] * tg.nt[1] * tg.nt[2]);
-    // The per-cell deposit pays where cells hold many particles, which share
-    // one row update per cell, and where the deposit is the wide order-3
-    // window in FP32: 256^3, 8 per cell, 21.2 -> 16.6 ms.  It loses at low
-    // densities (the laser box, 2 per cell: 4.65 -> 5.0 ms; 512^3, 2 per
-    // cell: 76.4 -> 78.2 ms), at order 1 (32^3 FP64: 0.049 -> 0.069 ms) and
-    // in FP64 (213 registers: 31.0 against 30.9 ms at 256^3, 0.35 -> 0.38 ms
-    // at 64^3 / 4 per cell).
+    // FP32 order 3 runs on the matrix cores (256^3, 8 per cell: 15.1 -> 12.8
+    // ms; 512^3, 2 per cell: 60.0 -> 44.4 ms) unless the tile is too large
+    // for it.  There the per-cell deposit pays where cells hold many
+    // particles, which share one row update per cell: 256^3, 8 per cell,
+    // 21.2 -> 16.6 ms.  It loses at low densities (the laser box, 2 per
+    // cell: 4.65 -> 5.0 ms), at order 1 (32^3 FP64: 0.049 -> 0.069 ms) and in
+    // FP64 (213 registers: 31.0 against 30.9 ms at 256^3, 0.35 -> 0.38 ms at
+    // 64^3 / 4 per cell).
     if constexpr (sizeof(T) == 4 && O == 3) {
+        if (quads_fit(tg, in.n))
+            return launch_particles_quads(pc, tg, in, out, f, tile_start, stray.p, stray.cnt, g, scratch, err, st);
         const int64_t ncell = (int64_t)tg.nt[0] * tg.t[0] * tg.nt[1] * tg.t[1] * tg.nt[2] * tg.t[2];
         TileGeo tq;
         const int kc = cells_chunk<T>(tg, tq);

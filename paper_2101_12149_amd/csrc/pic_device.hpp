@@ -426,6 +426,9 @@ struct EskAxis {
     bool cross;   // the particle changed cell along this axis
 };
 
+// Without branches on kappa: the lanes of a wave of cell-changing particles
+// take all three values along every axis, and each branch would run for the
+// whole wave.
 template <int O, typename T>
 __device__ inline void esk_axis(T d0, T d1, int kappa, EskAxis<O, T> &e)
 {
@@ -433,46 +436,26 @@ __device__ inline void esk_axis(T d0, T d1, int kappa, EskAxis<O, T> &e)
     constexpr int NW = S::NW;
     T w0[NW], qa[NW], qb[NW];
     S::w(d0, w0);
-#pragma unroll
-    for (int a = 0; a <= NW; ++a) {
-        e.S0[a] = T(0);
-        e.DS[a] = T(0);
-    }
+    const bool down = kappa < 0;
     e.cross = kappa != 0;
-    if (kappa == 0) {
-        S::q(d0, d1, qa);
-        const T dd = d1 - d0;
+    e.lo = down ? S::NB - 1 : S::NB;
+    // the old cell from d0 to d1 or to the face it leaves through, then the
+    // new cell from that face (its other side) to d1
+    const T ea = kappa == 0 ? d1 : (down ? T(0) : T(1)), eb = down ? T(1) : T(0);
+    S::q(d0, ea, qa);
+    S::q(eb, d1, qb);
+    const T da = ea - d0, db = kappa == 0 ? T(0) : d1 - eb;
+    // a window one node lower when the particle moves down
+    T carry = T(0);
 #pragma unroll
-        for (int a = 0; a < NW; ++a) {
-            e.S0[a] = w0[a];
-            e.DS[a] = dd * qa[a];
-        }
-        e.lo = S::NB;
-    } else if (kappa > 0) {
-        // old cell from d0 to its upper face, then new cell from 0 to d1
-        S::q(d0, T(1), qa);
-        S::q(T(0), d1, qb);
-        const T da = T(1) - d0;
-#pragma unroll
-        for (int a = 0; a < NW; ++a) {
-            e.S0[a] = w0[a];
-            e.DS[a] += da * qa[a];
-            e.DS[a + 1] += d1 * qb[a];
-        }
-        e.lo = S::NB;
-    } else {
-        // old cell from d0 down to its lower face, then new cell from 1 to d1
-        S::q(d0, T(0), qa);
-        S::q(T(1), d1, qb);
-        const T db = d1 - T(1);
-#pragma unroll
-        for (int a = 0; a < NW; ++a) {
-            e.S0[a + 1] = w0[a];
-            e.DS[a + 1] += -d0 * qa[a];
-            e.DS[a] += db * qb[a];
-        }
-        e.lo = S::NB - 1;
+    for (int a = 0; a < NW; ++a) {
+        const T x = da * qa[a], y = db * qb[a];
+        e.DS[a] = carry + (down ? y : x);
+        carry = down ? x : y;
+        e.S0[a] = down ? (a > 0 ? w0[a > 0 ? a - 1 : 0] : T(0)) : w0[a];
     }
+    e.DS[NW] = carry;
+    e.S0[NW] = down ? w0[NW - 1] : T(0);
 }
 
 // Derivatives of the window S0 and DS with respect to d0 and d1 (adjoint).

@@ -105,6 +105,14 @@ hipError_t launch_particles_tile(int order, const PConst<T> &pc, const TileGeo &
                                  const PArr<T> &out, const FieldPtrs<T> &f, const int *tile_start,
                                  int *stray_list, int *stray_cnt, const GuestArgs &g, T *const scratch[3], int *err,
                                  hipStream_t st);
+// The FP32 third-order tile step on the matrix cores (kernels_quads.hip), where
+// the tile's regions fit its LDS layout; arguments as above (stray_cnt
+// cleared by the caller).
+bool quads_fit(const TileGeo &tg, int64_t n);
+hipError_t launch_particles_quads(const PConst<float> &pc, const TileGeo &tg, const PArr<float> &in,
+                                  const PArr<float> &out, const FieldPtrs<float> &f, const int *tile_start,
+                                  int *stray_list, int *stray_cnt, const GuestArgs &g, float *const scratch[3],
+                                  int *err, hipStream_t st);
 // the particles the tile kernel listed, on global memory
 template <typename T>
 hipError_t launch_particles_strays(int order, const PConst<T> &pc, const PArr<T> &in, const PArr<T> &out,

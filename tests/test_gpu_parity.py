@@ -643,6 +643,109 @@ def test_dense_hot_tiles_overflow_the_crossing_queue(dtype):
         assert np.linalg.norm(drho + divJ) / np.linalg.norm(drho) < 1e-6
 
 
+@pytest.mark.parametrize("case", [
+    # grid, tile, slack, particles, cells they sit in (0: all), weights, Vay, steps
+    ((16, 16, 16), (8, 8, 8), 1, 1, 0, True, False, 1),         # a single particle, empty tiles
+    ((16, 16, 16), (8, 8, 8), 1, 8200, 0, True, False, 3),      # shared layout, constant pitches; guests
+    ((16, 16, 16), (8, 8, 8), 1, 28000, 0, False, True, 1),     # dense layout, constant pitches
+    ((16, 16, 16), (8, 8, 8), 1, 12000, 5, False, False, 3),    # few cells hold all: several rounds, long groups
+    ((10, 14, 10), (5, 7, 5), -1, 5600, 0, True, True, 3),      # ragged tiles, pitches from the arguments
+    ((10, 14, 10), (5, 7, 5), 2, 30000, 0, False, False, 1),    # ... in several rounds
+    ((12, 8, 8), (4, 4, 4), -1, 700, 0, False, False, 3),       # fewest threads
+    ((12, 8, 8), (4, 4, 4), 0, 9000, 0, True, False, 1),        # ... and a dense load, no slack
+    ((4, 8, 12), (4, 8, 4), 2, 2400, 0, True, False, 3),        # regions wrap more than once
+    ((16, 16, 20), (8, 8, 10), 0, 15000, 0, True, False, 1),    # the largest tile taken
+    ((16, 16, 18), (8, 8, 9), 0, 40000, 0, True, False, 1),     # ... in several rounds of the dense layout
+    ((24, 16, 8), (12, 8, 8), 0, 22000, 0, True, False, 1),     # too large a tile: the other kernels
+])
+def test_f32_order3_tile_step_matches_oracle(case):
+    """The FP32 third-order tile step over its layouts: rounds, group lengths,
+    pitches and tile edges, on a binning that is stale (a fifth of the
+    particles sit up to two cells from where they were binned: in the slack,
+    or outside it).  Per step: E, B, J within rel-L2 1e-5; momenta within
+    4e-6 of their scale (the bounds of gather and push, 2e-6 each) and
+    positions within 5e-6 cells (the push's 2e-6 and the momentum's error
+    times less than 0.6 cells a step); particle by particle, in place."""
+    n, tile, slack, npart, ncells, weights, vay, nsteps = case
+    g = dataclasses.replace(wl.plasma_grid(n, 3), pusher=int(vay))
+    g.tile, g.slack = tile, slack
+    rng = np.random.default_rng(131)
+    cells = None
+    if ncells:
+        few = np.stack([rng.integers(0, n[d], ncells) for d in range(3)])
+        cells = torch.tensor(few[:, rng.integers(0, ncells, npart)].astype(np.int32))
+    sp = dev(random_species(g, npart, 132, u_th=0.2, dtype="f32", weights=weights, cells=cells))
+    ts = torch.zeros(_lib.pic_tile_count(g, "f32") + 1, dtype=torch.int32, device="cuda")
+    _lib.pic_sort_tiles(g, sp, ts, _lib.workspace(g, "f32", npart))
+    shift = np.where(rng.random((1, npart)) < 0.2, rng.integers(-2, 3, (3, npart)), 0)
+    moved = (sp.cell.cpu().numpy() + shift) % np.array(n)[:, None]
+    start = wl.Species(torch.tensor(moved.astype(np.int32)), sp.off.cpu(), sp.u.cpu(),
+                       sp.w.cpu() if weights else None, sp.w0, sp.q, sp.m)
+    w = wl.Workload("geometry", g, start, random_fields(g, 133, scale=0.05, dtype="f32"), None, nsteps, 0, "f32", 131)
+    gsp, gf, _ = _run_gpu_steps(w, nsteps, 0, tile_start=ts)
+    osp, of, _ = _run_oracle(w, nsteps)
+    for name in ("E", "B", "J"):
+        assert rel_l2(_cpu(getattr(gf, name)), getattr(of, name)) < 1e-5 * nsteps, name
+    assert max_rel(_cpu(gsp.u), osp.u) < 4e-6 * nsteps
+    dx = np.abs(gsp.cell.cpu().numpy() + _cpu(gsp.off) - osp.cell - osp.off)
+    assert np.minimum(dx, np.abs(dx - np.array(n)[:, None])).max() < 5e-6 * nsteps
+
+
+@pytest.mark.parametrize("npart", [8200, 28000])
+def test_f32_order3_tile_step_leaves_corrupt_particles_out(npart):
+    """Corrupt particles among others of their cells, in both layouts: a state
+    error, they stay as they are, and the others' fields are the oracle's
+    without them."""
+    g = dataclasses.replace(wl.plasma_grid((16, 16, 16), 3))
+    g.tile, g.slack = (8, 8, 8), 1
+    sp = dev(random_species(g, npart, 141, u_th=0.1, dtype="f32"))
+    ts = torch.zeros(_lib.pic_tile_count(g, "f32") + 1, dtype=torch.int32, device="cuda")
+    ws = _lib.workspace(g, "f32", npart)
+    _lib.pic_sort_tiles(g, sp, ts, ws)
+    bad = [11, 500, 4000]
+    sp.u[1, bad[0]] = float("nan")
+    sp.off[0, bad[1]] = 1.5
+    sp.cell[2, bad[2]] = 16
+    f = random_fields(g, 142, scale=0.05, dtype="f32")
+    before, gf = sp.clone(), dev(f)
+    with pytest.raises(_lib.PicError) as ei:
+        _lib.pic_step(g, sp, gf, None, 0, 1, 0, ts, ws, None)
+    assert ei.value.name == "PIC_E_STATE"
+    keep = torch.ones(npart, dtype=torch.bool)
+    keep[bad] = False
+    for a, b in ((sp.cell, before.cell), (sp.off, before.off), (sp.u, before.u)):
+        assert torch.equal(a.cpu()[:, ~keep].nan_to_num(-7.0), b.cpu()[:, ~keep].nan_to_num(-7.0))
+    o = wl.Species(before.cell.cpu()[:, keep].contiguous(), before.off.cpu()[:, keep].contiguous(),
+                   before.u.cpu()[:, keep].contiguous(), before.w.cpu()[keep].contiguous(), before.w0, before.q,
+                   before.m).numpy()
+    of = f.numpy()
+    oracle.step(g, o, of, None, 0, 1)
+    assert rel_l2(_cpu(gf.J), of.J) < 1e-5
+    assert max_rel(_cpu(sp.u)[:, keep.numpy()], o.u) < 4e-6
+
+
+@pytest.mark.parametrize("ppc", [2, 8])
+def test_f32_order3_particles_that_end_at_a_cell_face(ppc):
+    """Every particle ends within a few roundings of a face of its cell, on
+    either side, so that which side it is decided by the last bits: the two
+    halves of the step agree on it (J within rel-L2 1e-5 of the oracle's, in
+    which a particle on the wrong side would miss a whole cell)."""
+    g = wl.plasma_grid((32, 32, 32), 3)
+    n = 32 ** 3 * ppc
+    sp = random_species(g, n, 151, u_th=0.2, dtype="f32")
+    u = sp.u.double()
+    disp = g.dt / g.d[0] * u / torch.sqrt(1.0 + (u ** 2).sum(0))
+    gen = torch.Generator().manual_seed(152)
+    face = torch.where(disp > 0, 1.0, 0.0) - disp
+    off = face.float() + torch.randint(-3, 4, (3, n), generator=gen).float() * 2.0 ** -25
+    sp.off = off.clamp(0.0, 1.0 - 2.0 ** -24).contiguous()
+    f = wl.Fields(*(torch.zeros((3, 32, 32, 32), dtype=torch.float32) for _ in range(3)))
+    w = wl.Workload("faces", g, sp, f, None, 1, 1, "f32", 151)
+    gsp, gf, _ = _run_gpu_steps(w, 1, 1)
+    osp, of, _ = _run_oracle(w, 1)
+    assert rel_l2(_cpu(gf.J), of.J) < 1e-5
+
+
 def test_guest_lists_overflow_to_the_stray_path():
     """64 ppc at u_th = 0.9c on 16^3, sorted once and then stepped without
     re-sorting: thousands of particles per tile leave their home region each
