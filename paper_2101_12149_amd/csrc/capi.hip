@@ -224,6 +224,45 @@ void region_extents(int order, TileGeo &tg)
     tg.jp = tg.rj[0];
 }
 
+// LDS layout of the one-pass tile kernel.  Lanes are consecutive cells along
+// x, then y, then z: with pitches that equal the tile's modulo 32 words (rows
+// of six interleaved field components, planes), consecutive lanes fall on
+// consecutive banks.  The rows of a current component are too short for that
+// on wide tiles; folded rows of 16 values do the same there.  What is left
+// over holds the queue of cell-crossing particles, up to 1024: two ints each,
+// and their offsets too where there is room (first order, and tiles of at
+// most 64 cells, which take 256).  Where the padded regions leave room for
+// less than 256, the rows stay unpadded.
+void tile_layout(GridInfo &gi, size_t limit)
+{
+    TileGeo &tg = gi.tg;
+    const int banks = 128 / (int)gi.tsize;   // values
+    for (int pad = 1; pad >= 0; --pad) {
+        tg.pr = 6 * tg.rf[0];
+        tg.jq = tg.rj[0];
+        tg.fold = 0;
+        if (pad) {
+            tg.pr += (tg.t[0] + banks - tg.pr % banks) % banks;
+            if (gi.order == 3 && tg.t[0] > 4 && tg.rj[0] <= 16 && tg.rj[1] % 2 == 1) {
+                tg.jq = 16;
+                tg.fold = 8;
+            }
+        }
+        tg.ps = tg.pr * tg.rf[1];
+        if (pad)
+            tg.ps += (tg.t[0] * tg.t[1] + banks - tg.ps % banks) % banks;
+        const size_t used = (((size_t)tg.ps * tg.rf[2] * gi.tsize + 15) & ~size_t(15)) +
+                            tile_current_values(tg) * sizeof(double) + sizeof(int);
+        const bool small = tg.t[0] * tg.t[1] * tg.t[2] <= 64;
+        tg.qoff = small || gi.order == 1;
+        const size_t entry = 2 * sizeof(int) + (tg.qoff ? 6 * gi.tsize : 0), most = small ? 256 : 1024;
+        const size_t room = limit > used ? (limit - used) / entry : 0;
+        tg.qcap = (int)(room < most ? room : most);
+        if (tg.qcap >= 256)
+            break;
+    }
+}
+
 // LDS of the tiled adjoint: its first pass holds E, B with the gather halo
 // and hatE with the deposit halo, its second the FP64 accumulators of the
 // six field adjoints
@@ -369,14 +408,7 @@ pic_status check_grid(const pic_grid *g, GridInfo &gi)
         gi.tg.t[dmax] /= 2;
         region_extents(gi.order, gi.tg);
     }
-    // the LDS left over holds the forward tile kernel's queue of
-    // cell-crossing particles (up to 1024 entries)
-    {
-        const size_t used = lds_bytes(gi) + sizeof(int);
-        const size_t entry = 6 * gi.tsize + 2 * sizeof(int);
-        const size_t room = limit > used ? (limit - used) / entry : 0;
-        gi.tg.qcap = (int)(room < 1024 ? room : 1024);
-    }
+    tile_layout(gi, limit);
     int nt = 1;
     for (int d = 0; d < 3; ++d) {
         gi.tg.nt[d] = gi.n[d] / gi.tg.t[d];

@@ -26,11 +26,17 @@ constexpr int STRAY_THREADS = 256;
 // thread takes about one cell's particles, so neighbouring lanes touch
 // neighbouring LDS words
 constexpr int TILE_THREADS = 512;
-// FP32 fits the fused step in 128 registers, so its tiles run 16 waves per CU;
-// FP64 needs more registers and runs 8
-template <typename T>
+// Threads of a tile workgroup.  FP32 fits the fused step in 128 registers, so
+// its tiles run 16 waves per CU; FP64 at third order fits 168 (12 waves), and
+// its first-order tiles are small enough for two workgroups.
+template <typename T, int O>
 struct TileThreads {
-    static constexpr int value = sizeof(T) == 4 ? 1024 : 512;
+    static constexpr int value = sizeof(T) == 4 ? 1024 : O == 3 ? 768 : 512;
+};
+
+template <typename T>
+struct Off3 {
+    T *o[3];
 };
 
 // ---------------------------------------------------------------------------
@@ -39,17 +45,20 @@ struct TileThreads {
 // Esirkepov window would make every wave issue the rim's LDS atomics with
 // only those lanes active.  The tile kernel deposits the particles that stay
 // in their cells with the narrow window and queues the others (their
-// in-tile index, local cell, cell change and old / new offsets), then
-// deposits the queue in full waves.  A particle that finds the queue full
-// is deposited at once.
+// in-tile index, local cell and cell change), then deposits the queue in full
+// waves.  A particle that finds the queue full is deposited at once.  The
+// offsets stay in memory, the old ones in scratch (`keep`) when the step runs
+// in place; a queue with room for them (small tiles, whose workgroups would
+// wait out the round trip at their end) holds them itself.
 template <typename T>
 struct CrossQueue {
     int *cnt;
     int cap;
     int *j, *pk;
-    T *f0, *f1;   // [3][cap]
+    T *f0, *f1;   // [3][cap], or null
 
-    __device__ bool push(int jj, const int *l, const int *kap, const T *a, const T *b) const
+    __device__ bool push(int jj, const int *l, const int *kap, const T *a, const T *b, const Off3<T> &keep,
+                         const Off3<T> &in, int64_t p) const
     {
         const int i = atomicAdd(cnt, 1);
         if (i >= cap)
@@ -58,10 +67,23 @@ struct CrossQueue {
         pk[i] = pack(l, kap);
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            f0[d * cap + i] = a[d];
-            f1[d * cap + i] = b[d];
+            if (f0) {
+                f0[d * cap + i] = a[d];
+                f1[d * cap + i] = b[d];
+            } else if (keep.o[d] != in.o[d]) {
+                keep.o[d][p] = a[d];
+            }
         }
         return true;
+    }
+    // offsets of entry i, particle p
+    __device__ void offsets(int i, int64_t p, const Off3<T> &keep, T *const *out, T *a, T *b) const
+    {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            a[d] = f0 ? f0[d * cap + i] : keep.o[d][p];
+            b[d] = f0 ? f1[d * cap + i] : out[d][p];
+        }
     }
     // local cell + 8 in 5 bits and the cell change + 1 in 2 bits per axis
     __device__ static int pack(const int *l, const int *kap)
@@ -83,11 +105,12 @@ struct CrossQueue {
     }
 };
 
-// Esirkepov deposit with the full window into the LDS current tile; with
-// MSEL in 0..2 only that component
+// Esirkepov deposit with the full window into the LDS current tile (its
+// indices folded by `fold`, see lds_fold); with MSEL in 0..2 only that
+// component
 template <typename T, int O, int MSEL = -1>
 __device__ __attribute__((always_inline)) inline void deposit_local_full(const PConst<T> &pc, const T *f0, const T *f1, const int *kap,
-                                          const int *l, int lo_j, const int *sj, T w, double *sJ, int rjvol)
+                                          const int *l, int lo_j, const int *sj, T w, double *sJ, int rjvol, int fold = 0)
 {
     constexpr int NW = Shape<O, T>::NW;
     EskAxis<O, T> e[3];
@@ -99,7 +122,16 @@ __device__ __attribute__((always_inline)) inline void deposit_local_full(const P
         K[d] = pc.jk[d] * w;
         axis_offsets_local<NW + 1>(l[d] + lo_j, e[d].lo, sj[d], jo[d]);
     }
-    esk_scatter<O, T, double, MSEL>(e, jo, K,
+    // (as for deposit_still_shared: the rows of the window alternate)
+    const int even = ((jo[1][0] + jo[2][0]) >> 1) & fold, odd = even ^ fold;
+    int xe[NW + 1], xo[NW + 1];
+#pragma unroll
+    for (int a = 0; a <= NW; ++a) {
+        xe[a] = jo[0][a] ^ even;
+        xo[a] = jo[0][a] ^ odd;
+    }
+    const int *const jx[2] = {xe, xo};
+    esk_scatter<O, T, double, MSEL>(e, jo, jx, K,
                                     [&](int m, int idx, double v) { latomic_add(sJ + m * rjvol + idx, v); });
 }
 
@@ -182,7 +214,8 @@ __device__ __attribute__((always_inline)) inline void particle_step_global(const
         K[d] = pc.jk[d] * w;
         axis_offsets_global<NW + 1>(c[d], e[d].lo, pc.n[d], gs[d], jo[d]);
     }
-    esk_scatter<O, T, T>(e, jo, K, [&](int m, int idx, T v) { gatomic_add(fp.J[m] + idx, v); });
+    const int *const jx[2] = {jo[0], jo[0]};
+    esk_scatter<O, T, T>(e, jo, jx, K, [&](int m, int idx, T v) { gatomic_add(fp.J[m] + idx, v); });
 }
 
 // ---------------------------------------------------------------------------
@@ -267,9 +300,9 @@ __device__ inline XRun xrun(int key)
 // and lane R-d writes e_R[d+1] (node X_R + d + 1) in a second instruction,
 // so a row costs two LDS instructions; a run shorter than NT - 1 lanes
 // leaves the rest to its last lane.  V is the type the row is summed in; the
-// LDS accumulators are FP64.
-template <int NT, typename V>
-__device__ __attribute__((always_inline)) inline void xrow_add(double *row, const V *r, const XRun &xr)
+// LDS accumulators are FP64: at(k) is the address of the row's node k.
+template <int NT, typename V, typename AtFn>
+__device__ __attribute__((always_inline)) inline void xrow_add_at(AtFn &&at, const V *r, const XRun &xr)
 {
     V e[NT];
     e[NT - 1] = r[NT - 1];
@@ -279,7 +312,7 @@ __device__ __attribute__((always_inline)) inline void xrow_add(double *row, cons
         const V snd = xr.send ? e[k + 1] : V(0);
         e[k] = r[k] + dpp_shift<1>(snd);
     }
-    latomic_add(row, (double)e[0]);
+    latomic_add(at(0), (double)e[0]);
     if constexpr (NT >= 2) {
         V x = e[1];
         int off = xr.d == 0 ? 1 : -1;
@@ -305,14 +338,21 @@ __device__ __attribute__((always_inline)) inline void xrow_add(double *row, cons
             }
         }
         if (off > 0)
-            latomic_add(row + off, (double)x);
+            latomic_add(at(off), (double)x);
         if (xr.last && xr.len < NT - 1) {
 #pragma unroll
             for (int k = 2; k < NT; ++k)
                 if (k > xr.len)
-                    latomic_add(row + k, (double)e[k]);
+                    latomic_add(at(k), (double)e[k]);
         }
     }
+}
+
+// the same for a row of consecutive addresses
+template <int NT, typename V>
+__device__ __attribute__((always_inline)) inline void xrow_add(double *row, const V *r, const XRun &xr)
+{
+    xrow_add_at<NT>([&](int k) { return row + k; }, r, xr);
 }
 
 // The same row on global memory: add(k, v) adds v to node k of this lane's
@@ -351,7 +391,8 @@ __device__ inline int xrun_key_global(const int *st, const int *n)
 // FP64 accumulators.
 template <typename T, int O>
 __device__ __attribute__((always_inline)) inline void deposit_still_shared(const PConst<T> &pc, const T *f0, const T *f1, const int *l,
-                                            int lo_j, const int *sj, T w, double *sJ, int rjvol, const XRun &xr)
+                                            int lo_j, const int *sj, T w, double *sJ, int rjvol, const XRun &xr,
+                                            int fold = 0)
 {
     constexpr int NW = Shape<O, T>::NW;
     const T half = T(0.5), third = T(1) / T(3);
@@ -378,6 +419,13 @@ __device__ __attribute__((always_inline)) inline void deposit_still_shared(const
     auto cw = [&](int p, int q, int b, int c) -> T {
         return S0[p][b] * (S0[q][c] + half * DS[q][c]) + DS[p][b] * (half * S0[q][c] + third * DS[q][c]);
     };
+    // (the row length along y is odd where rows are folded, so that the rows
+    // of the window alternate along both axes)
+    const int even = ((jo[1][0] + jo[2][0]) >> 1) & fold, odd = even ^ fold;
+    auto row = [&](int m, int yz, int alt, const auto &r) {
+        xrow_add_at<(int)(sizeof(r) / sizeof(r[0]))>(
+            [&](int k) { return sJ + m * rjvol + yz + ((jo[0][0] + k) ^ (alt & 1 ? odd : even)); }, r, xr);
+    };
     // J_x (p = y, q = z): rows along x are the taps a
 #pragma unroll
     for (int c = 0; c < NW; ++c)
@@ -388,7 +436,7 @@ __device__ __attribute__((always_inline)) inline void deposit_still_shared(const
 #pragma unroll
             for (int a = 0; a < NW - 1; ++a)
                 r[a] = P[0][a] * C;
-            xrow_add<NW - 1>(sJ + jo[1][b] + jo[2][c] + jo[0][0], r, xr);
+            row(0, jo[1][b] + jo[2][c], b + c, r);
         }
     // J_y (p = z, q = x): rows along x are the taps c
 #pragma unroll
@@ -399,7 +447,7 @@ __device__ __attribute__((always_inline)) inline void deposit_still_shared(const
 #pragma unroll
             for (int c = 0; c < NW; ++c)
                 r[c] = P[1][a] * cw(2, 0, b, c);
-            xrow_add<NW>(sJ + rjvol + jo[2][b] + jo[1][a] + jo[0][0], r, xr);
+            row(1, jo[2][b] + jo[1][a], a + b, r);
         }
     // J_z (p = x, q = y): rows along x are the taps b
 #pragma unroll
@@ -410,33 +458,42 @@ __device__ __attribute__((always_inline)) inline void deposit_still_shared(const
 #pragma unroll
             for (int b = 0; b < NW; ++b)
                 r[b] = P[2][a] * cw(0, 1, b, c);
-            xrow_add<NW>(sJ + 2 * rjvol + jo[1][c] + jo[2][a] + jo[0][0], r, xr);
+            row(2, jo[1][c] + jo[2][a], a + c, r);
         }
 }
 
 // ---------------------------------------------------------------------------
+// The one-pass tile step.  In FP64 at third order the LDS pipe bounds it: a
+// wave's 384 field reads and some 200 atomics kept it 82 % busy, half of that
+// time on bank conflicts, against 37 % for the vector unit.  With the padded
+// and folded rows of tile_layout (which take 43 % of the conflict cycles away)
+// and 12 waves, 128^3 / 8 per cell went from 3.74 to 3.18 ms a step, 64^3 / 4
+// per cell from 282 to 250 us.  Staggered windows along y at five
+// fixed rows, which never conflict, read more than they saved (3.22 ms).
+//
 // The particles left to k_particles_strays are listed (`strays`) before they
 // move: when the step runs in place their cells are overwritten, so the
 // stray kernel could not tell them from the cells any more.
-template <typename T, int O, bool G>
-__global__ void __launch_bounds__(TileThreads<T>::value) k_particles_tile(PConst<T> pc, TileGeo tg, PArr<T> in, PArr<T> out,
+template <typename T, int O, bool G, int NTH>
+__global__ void __launch_bounds__(NTH) k_particles_tile(PConst<T> pc, TileGeo tg, PArr<T> in, PArr<T> out,
                                                         FieldPtrs<T> fp, const int *__restrict__ tile_start,
-                                                        StrayList strays, GuestArgs g, int *err)
+                                                        StrayList strays, GuestArgs g, Off3<T> f0s, int *err)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T *sF = reinterpret_cast<T *>(smem_raw);
-    const int rfx = tg.rf[0], rfy = tg.rf[1];
-    const int rfvol = rfx * rfy * tg.rf[2];
-    const int rjx = tg.rj[0], rjy = tg.rj[1], jpx = tg.jp;
-    const int rjvol = jpx * rjy * tg.rj[2];   // rows padded to jp values
+    const int rjx = tg.rj[0], rjy = tg.rj[1];
+    const int rjvol = tg.jq * rjy * tg.rj[2], rjall = tile_current_values(tg);
     // the current tile accumulates in FP64 (fast LDS atomics), after the fields
-    double *sJ = reinterpret_cast<double *>(smem_raw + ((6 * rfvol * sizeof(T) + 15) & ~size_t(15)));
-    // then the queue of cell-crossing particles: offsets, indices, count
+    double *sJ = reinterpret_cast<double *>(smem_raw + ((tg.ps * tg.rf[2] * sizeof(T) + 15) & ~size_t(15)));
+    // (first-order tiles are not folded, and their queue holds the offsets)
+    const int fold = O == 3 ? tg.fold : 0;
+    const bool qoff = O == 1 || tg.qoff;
+    // then the queue of cell-crossing particles: offsets, indices, moves, count
     CrossQueue<T> cq;
     cq.cap = tg.qcap;
-    cq.f0 = reinterpret_cast<T *>(sJ + 3 * rjvol);
-    cq.f1 = cq.f0 + 3 * cq.cap;
-    cq.j = reinterpret_cast<int *>(cq.f1 + 3 * cq.cap);
+    cq.f0 = qoff ? reinterpret_cast<T *>(sJ + rjall) : nullptr;
+    cq.f1 = qoff ? cq.f0 + 3 * cq.cap : nullptr;
+    cq.j = reinterpret_cast<int *>(reinterpret_cast<T *>(sJ + rjall) + (qoff ? 6 * cq.cap : 0));
     cq.pk = cq.j + cq.cap;
     cq.cnt = cq.pk + cq.cap;
     const TileSpan ts = tile_span(tg, tile_start, in.n);
@@ -446,15 +503,8 @@ __global__ void __launch_bounds__(TileThreads<T>::value) k_particles_tile(PConst
         return;   // uniform across the workgroup
 
     const int tid = threadIdx.x, nth = blockDim.x;
-    region_walk(pc.n, ts.t0, tg.lo_f, rfx, rfy, tg.rf[2], rfx, region_wraps_once(pc.n, tg.t, tg.lo_f, tg.rf),
-                [&](int r, int gi) {
-#pragma unroll
-                    for (int m = 0; m < 3; ++m) {
-                        sF[m * rfvol + r] = fp.E[m][gi];
-                        sF[(3 + m) * rfvol + r] = fp.B[m][gi];
-                    }
-                });
-    for (int r = tid; r < 3 * rjvol; r += nth)
+    stage_fields<O == 1 ? 1 : sizeof(T) == 4 ? 4 : 2>(fp, pc.n, tg, ts.t0, sF, tg.rf[0], tg.pr, tg.ps);
+    for (int r = tid; r < rjall; r += nth)
         sJ[r] = 0.0;
     if (tid == 0)
         *cq.cnt = 0;
@@ -463,10 +513,11 @@ __global__ void __launch_bounds__(TileThreads<T>::value) k_particles_tile(PConst
     FieldSrc<T> lf;
 #pragma unroll
     for (int m = 0; m < 6; ++m)
-        lf.c[m] = sF + m * rfvol;
-    const int sf[3] = {1, rfx, rfx * rfy};
-    const int sj[3] = {1, jpx, jpx * rjy};
+        lf.c[m] = sF + m * tg.rf[0];
+    const int sf[3] = {1, tg.pr, tg.ps};
+    const int sj[3] = {1, tg.jq, tg.jq * rjy};
     const int np = (int)(ts.pe - ts.ps);
+    const Off3<T> fin = {{in.off[0], in.off[1], in.off[2]}};
     // coalesced: the tile's particles are stored rank-major (one particle
     // per cell, cell after cell, then the next rank), so consecutive lanes
     // read consecutive memory and sit in distinct neighbouring cells.  After
@@ -517,8 +568,8 @@ __global__ void __launch_bounds__(TileThreads<T>::value) k_particles_tile(PConst
                 if (particle_advance<T, O, true>(pc, in, out, lf, p, c, f, u, l, tg.lo_f, sf, f1, kap, w, err)) {
                     if ((kap[0] | kap[1] | kap[2]) == 0)
                         key = xrun_key(l);
-                    else if (!cq.push((int)(p - ts.ps), l, kap, f, f1))
-                        deposit_local_full<T, O>(pc, f, f1, kap, l, tg.lo_j, sj, w, sJ, rjvol);
+                    else if (!cq.push((int)(p - ts.ps), l, kap, f, f1, f0s, fin, p))
+                        deposit_local_full<T, O>(pc, f, f1, kap, l, tg.lo_j, sj, w, sJ, rjvol, fold);
                     // a particle that changed cells, or a guest (outside its home
                     // region), gets its status for the next step
                     if (G && ((kap[0] | kap[1] | kap[2]) || !own)) {
@@ -541,7 +592,7 @@ __global__ void __launch_bounds__(TileThreads<T>::value) k_particles_tile(PConst
         stray_append(is_stray, pst, strays);
         const XRun xr = xrun(key);
         if (key != 0)
-            deposit_still_shared<T, O>(pc, f, f1, l, tg.lo_j, sj, w, sJ, rjvol, xr);
+            deposit_still_shared<T, O>(pc, f, f1, l, tg.lo_j, sj, w, sJ, rjvol, xr, fold);
     }
     __syncthreads();
     // deposit the queued cell-crossing particles in full waves, one lane per
@@ -554,25 +605,22 @@ __global__ void __launch_bounds__(TileThreads<T>::value) k_particles_tile(PConst
         int l[3], kap[3];
         CrossQueue<T>::unpack(cq.pk[k], l, kap);
         T f0[3], f1[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            f0[d] = cq.f0[d * cq.cap + k];
-            f1[d] = cq.f1[d * cq.cap + k];
-        }
+        cq.offsets(k, p, f0s, out.off, f0, f1);
         const T w = in.w ? in.w[p] : pc.w0;
         if (m == 0)
-            deposit_local_full<T, O, 0>(pc, f0, f1, kap, l, tg.lo_j, sj, w, sJ, rjvol);
+            deposit_local_full<T, O, 0>(pc, f0, f1, kap, l, tg.lo_j, sj, w, sJ, rjvol, fold);
         else if (m == 1)
-            deposit_local_full<T, O, 1>(pc, f0, f1, kap, l, tg.lo_j, sj, w, sJ, rjvol);
+            deposit_local_full<T, O, 1>(pc, f0, f1, kap, l, tg.lo_j, sj, w, sJ, rjvol, fold);
         else
-            deposit_local_full<T, O, 2>(pc, f0, f1, kap, l, tg.lo_j, sj, w, sJ, rjvol);
+            deposit_local_full<T, O, 2>(pc, f0, f1, kap, l, tg.lo_j, sj, w, sJ, rjvol, fold);
     }
     __syncthreads();
-    region_walk(pc.n, ts.t0, tg.lo_j, rjx, rjy, tg.rj[2], jpx, region_wraps_once(pc.n, tg.t, tg.lo_j, tg.rj),
+    region_walk(pc.n, ts.t0, tg.lo_j, rjx, rjy, tg.rj[2], tg.jq, region_wraps_once(pc.n, tg.t, tg.lo_j, tg.rj),
                 [&](int r, int gi) {
+                    const double *s = sJ + lds_fold(r, fold);
 #pragma unroll
                     for (int m = 0; m < 3; ++m) {
-                        const T v = (T)sJ[m * rjvol + r];
+                        const T v = m < 2 || r < rjall - 2 * rjvol ? (T)s[m * rjvol] : T(0);
                         if (v != T(0))
                             gatomic_add(fp.J[m] + gi, v);
                     }
@@ -640,14 +688,9 @@ __device__ inline void block_exclusive_scan(const int *in, int *out, int n, int 
 // order of the sums changes.  Particles are taken in chunks of `kc` (the
 // list capacity); each chunk runs both phases.
 
-template <typename T>
-struct Off3 {
-    T *o[3];
-};
-
 // LDS layout of k_particles_cells (byte offsets), shared by the launcher
 struct CellsLds {
-    size_t f, a, cnt, start, sh, keys, list, qf0, qf1, qj, qpk, qcnt, total;
+    size_t f, a, cnt, start, sh, keys, list, qj, qpk, qcnt, total;
 };
 
 __host__ __device__ inline CellsLds cells_lds(const TileGeo &tg, int nth, int kc, int tsize)
@@ -662,10 +705,6 @@ __host__ __device__ inline CellsLds cells_lds(const TileGeo &tg, int nth, int kc
     o = al16(o + 6 * rf * tsize);
     L.a = o;
     o = al16(o + rj * sizeof(double));
-    L.qf0 = o;
-    o = al16(o + 3 * (size_t)tg.qcap * tsize);
-    L.qf1 = o;
-    o = al16(o + 3 * (size_t)tg.qcap * tsize);
     L.cnt = o;
     o += 4 * (tc + 1);
     L.start = o;
@@ -851,18 +890,14 @@ __device__ __attribute__((always_inline)) inline void cells_component(
         int l[3], kap[3];
         CrossQueue<T>::unpack(cq.pk[k], l, kap);
         T f0[3], f1[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            f0[d] = cq.f0[d * cq.cap + k];
-            f1[d] = cq.f1[d * cq.cap + k];
-        }
+        cq.offsets(k, p, f0s, out.off, f0, f1);
         const T w = in.w ? in.w[p] : pc.w0;
         deposit_local_comp<T, O, M>(pc, f0, f1, kap, l, tg.lo_j, sj, w, sA);
     }
 }
 
 template <typename T, int O, bool G>
-__global__ void __launch_bounds__(TileThreads<T>::value) k_particles_cells(PConst<T> pc, TileGeo tg, PArr<T> in,
+__global__ void __launch_bounds__((TileThreads<T, O>::value)) k_particles_cells(PConst<T> pc, TileGeo tg, PArr<T> in,
                                                                            PArr<T> out, FieldPtrs<T> fp,
                                                                            const int *__restrict__ tile_start,
                                                                            StrayList strays, GuestArgs g,
@@ -880,8 +915,8 @@ __global__ void __launch_bounds__(TileThreads<T>::value) k_particles_cells(PCons
     int *list = reinterpret_cast<int *>(smem_raw + Ld.list);
     CrossQueue<T> cq;
     cq.cap = tg.qcap;
-    cq.f0 = reinterpret_cast<T *>(smem_raw + Ld.qf0);
-    cq.f1 = reinterpret_cast<T *>(smem_raw + Ld.qf1);
+    cq.f0 = nullptr;   // (the offsets of all particles are in memory)
+    cq.f1 = nullptr;
     cq.j = reinterpret_cast<int *>(smem_raw + Ld.qj);
     cq.pk = reinterpret_cast<int *>(smem_raw + Ld.qpk);
     cq.cnt = reinterpret_cast<int *>(smem_raw + Ld.qcnt);
@@ -894,14 +929,7 @@ __global__ void __launch_bounds__(TileThreads<T>::value) k_particles_cells(PCons
     const int ng = (G && g.cnt) ? (g.cnt[ts.t] < g.cap ? g.cnt[ts.t] : g.cap) : 0;
     if (ts.pe <= ts.ps && ng == 0)
         return;   // uniform across the workgroup
-    region_walk(pc.n, ts.t0, tg.lo_f, rfx, rfy, tg.rf[2], rfx, region_wraps_once(pc.n, tg.t, tg.lo_f, tg.rf),
-                [&](int r, int gi) {
-#pragma unroll
-                    for (int m = 0; m < 3; ++m) {
-                        sF[m * rfvol + r] = fp.E[m][gi];
-                        sF[(3 + m) * rfvol + r] = fp.B[m][gi];
-                    }
-                });
+    stage_fields<O == 1 ? 1 : sizeof(T) == 4 ? 4 : 2>(fp, pc.n, tg, ts.t0, sF, rfvol, rfx, rfx * rfy);
     for (int r = tid; r < rjvol; r += nth)
         sA[r] = 0.0;
     FieldSrc<T> lf;
@@ -957,23 +985,19 @@ __global__ void __launch_bounds__(TileThreads<T>::value) k_particles_cells(PCons
             } else {
                 int kap[3];
                 if (particle_advance<T, O, true, false>(pc, in, out, lf, p, c, f, u, l, tg.lo_f, sf, f1, kap, w, err)) {
-                    if ((kap[0] | kap[1] | kap[2]) == 0) {
 #pragma unroll
-                        for (int d = 0; d < 3; ++d) {
-                            out.off[d][p] = f1[d];
-                            if (f0s.o[d] != in.off[d])
-                                f0s.o[d][p] = f[d];
-                        }
+                    for (int d = 0; d < 3; ++d) {
+                        out.off[d][p] = f1[d];
+                        if (f0s.o[d] != in.off[d])
+                            f0s.o[d][p] = f[d];
+                    }
+                    if ((kap[0] | kap[1] | kap[2]) == 0) {
                         const bool in_tile = l[0] >= 0 && l[0] < tg.t[0] && l[1] >= 0 && l[1] < tg.t[1] &&
                                              l[2] >= 0 && l[2] < tg.t[2];
                         const int slot = in_tile ? l[0] + tg.t[0] * (l[1] + tg.t[1] * l[2]) : tc;
                         key = (slot << 16) | atomicAdd(ccnt + slot, 1);
-                    } else {
-#pragma unroll
-                        for (int d = 0; d < 3; ++d)
-                            out.off[d][p] = f1[d];
-                        if (!cq.push((int)(p - ts.ps), l, kap, f, f1))
-                            deposit_global_full<T, O>(pc, fp, c, f, f1, kap, w);
+                    } else if (!cq.push((int)(p - ts.ps), l, kap, f, f1, f0s, f0s, p)) {
+                        deposit_global_full<T, O>(pc, fp, c, f, f1, kap, w);
                     }
                     if (G && ((kap[0] | kap[1] | kap[2]) || !own)) {
                         int c1[3], ht0[3] = {ts.t0[0], ts.t0[1], ts.t0[2]};
@@ -2298,20 +2322,19 @@ __global__ void __launch_bounds__(NTH) k_adjoint_push_tile(PConst<T> pc, TileGeo
     if (ts.pe <= ts.ps)
         return;   // uniform across the workgroup
     const int tid = threadIdx.x, nth = blockDim.x;
-    region_walk(pc.n, ts.t0, tg.lo_f, rfx, rfy, tg.rf[2], rfx, region_wraps_once(pc.n, tg.t, tg.lo_f, tg.rf),
-                [&](int r, int gi) {
+    stage_fields<O == 1 ? 1 : sizeof(T) == 4 ? 4 : 2>(fp, pc.n, tg, ts.t0, sF, rfvol, rfx, rfx * rfy);
+    region_stage<sizeof(T) == 4 ? 4 : 2, 3, T>(
+        pc.n, ts.t0, tg.lo_j, rjx, rjy, tg.rj[2], region_wraps_once(pc.n, tg.t, tg.lo_j, tg.rj),
+        [&](int gi, T *v) {
 #pragma unroll
-                    for (int m = 0; m < 3; ++m) {
-                        sF[m * rfvol + r] = fp.E[m][gi];
-                        sF[(3 + m) * rfvol + r] = fp.B[m][gi];
-                    }
-                });
-    region_walk(pc.n, ts.t0, tg.lo_j, rjx, rjy, tg.rj[2], rjx, region_wraps_once(pc.n, tg.t, tg.lo_j, tg.rj),
-                [&](int r, int gi) {
+            for (int m = 0; m < 3; ++m)
+                v[m] = ap.hat[m][gi];
+        },
+        [&](int x, int y, int z, const T *v) {
 #pragma unroll
-                    for (int m = 0; m < 3; ++m)
-                        sH[m * rjvol + r] = ap.hat[m][gi];
-                });
+            for (int m = 0; m < 3; ++m)
+                sH[m * rjvol + x + rjx * (y + rjy * z)] = v[m];
+        });
     __syncthreads();
     FieldSrc<T> lf;
 #pragma unroll
@@ -2721,10 +2744,8 @@ static inline unsigned nblk(int64_t n, int b)
 template <typename T>
 size_t tile_lds_bytes(int, const TileGeo &tg)
 {
-    const size_t rf = (size_t)tg.rf[0] * tg.rf[1] * tg.rf[2];
-    const size_t rj = (size_t)tg.jp * tg.rj[1] * tg.rj[2];
-    return ((6 * rf * sizeof(T) + 15) & ~size_t(15)) + 3 * rj * sizeof(double) +
-           (size_t)tg.qcap * (6 * sizeof(T) + 2 * sizeof(int)) + sizeof(int);
+    return (((size_t)tg.ps * tg.rf[2] * sizeof(T) + 15) & ~size_t(15)) + tile_current_values(tg) * sizeof(double) +
+           (size_t)tg.qcap * (2 * sizeof(int) + (tg.qoff ? 6 * sizeof(T) : 0)) + sizeof(int);
 }
 
 template <typename K>
@@ -2740,12 +2761,12 @@ static void allow_big_lds(K *kernel, bool &done)
 
 // the two-phase tile kernel's queue entries and the list capacity left by
 // its LDS; 0 when the list would hold fewer than 1024 particles
-template <typename T>
+template <typename T, int O>
 int cells_chunk(const TileGeo &tg, TileGeo &tq)
 {
     tq = tg;
     tq.qcap = sizeof(T) == 4 ? 512 : 256;
-    const size_t fixed = cells_lds(tq, TileThreads<T>::value, 0, (int)sizeof(T)).total;
+    const size_t fixed = cells_lds(tq, TileThreads<T, O>::value, 0, (int)sizeof(T)).total;
     const size_t limit = 160 * 1024;
     if (fixed >= limit)
         return 0;
@@ -2760,7 +2781,8 @@ static hipError_t launch_tile_o(const PConst<T> &pc, const TileGeo &tg, const PA
                                 const FieldPtrs<T> &f, const int *tile_start, const StrayList &stray,
                                 const GuestArgs &g, T *const scratch[3], int *err, hipStream_t st)
 {
-    static bool attr_plain = false, attr_guests = false, attr_cp = false, attr_cg = false;
+    static bool attr_plain = false, attr_guests = false, attr_few = false, attr_few_guests = false;
+    static bool attr_cp = false, attr_cg = false;
     const unsigned ntiles = (unsigned)(tg.nt[0] * tg.nt[1] * tg.nt[2]);
     // FP32 order 3 runs on the matrix cores (256^3, 8 per cell: 15.1 -> 12.8
     // ms; 512^3, 2 per cell: 60.0 -> 44.4 ms) unless the tile is too large
@@ -2770,44 +2792,54 @@ static hipError_t launch_tile_o(const PConst<T> &pc, const TileGeo &tg, const PA
     // cell: 4.65 -> 5.0 ms), at order 1 (32^3 FP64: 0.049 -> 0.069 ms) and in
     // FP64 (213 registers: 31.0 against 30.9 ms at 256^3, 0.35 -> 0.38 ms at
     // 64^3 / 4 per cell).
+    // the old offsets that a later phase needs wait in scratch when the step
+    // runs in place
+    Off3<T> f0s;
+    for (int d = 0; d < 3; ++d)
+        f0s.o[d] = in.off[d] == out.off[d] ? scratch[d] : in.off[d];
     if constexpr (sizeof(T) == 4 && O == 3) {
         if (quads_fit(tg, in.n))
             return launch_particles_quads(pc, tg, in, out, f, tile_start, stray.p, stray.cnt, g, scratch, err, st);
         const int64_t ncell = (int64_t)tg.nt[0] * tg.t[0] * tg.nt[1] * tg.t[1] * tg.nt[2] * tg.t[2];
         TileGeo tq;
-        const int kc = cells_chunk<T>(tg, tq);
+        const int kc = cells_chunk<T, O>(tg, tq);
         if (kc > 0 && in.n >= 6 * ncell) {
-            // the old offsets of the particles that stay in their cells wait
-            // in scratch when the step runs in place
-            Off3<T> f0s;
-            for (int d = 0; d < 3; ++d)
-                f0s.o[d] = in.off[d] == out.off[d] ? scratch[d] : in.off[d];
-            const size_t l = cells_lds(tq, TileThreads<T>::value, kc, (int)sizeof(T)).total;
+            const size_t l = cells_lds(tq, TileThreads<T, O>::value, kc, (int)sizeof(T)).total;
             if (g.flag_next) {
                 allow_big_lds(&k_particles_cells<T, O, true>, attr_cg);
-                hipLaunchKernelGGL((k_particles_cells<T, O, true>), dim3(ntiles), dim3(TileThreads<T>::value), l, st,
+                hipLaunchKernelGGL((k_particles_cells<T, O, true>), dim3(ntiles), dim3(TileThreads<T, O>::value), l, st,
                                    pc, tq, in, out, f, tile_start, stray, g, f0s, kc, err);
             } else {
                 allow_big_lds(&k_particles_cells<T, O, false>, attr_cp);
-                hipLaunchKernelGGL((k_particles_cells<T, O, false>), dim3(ntiles), dim3(TileThreads<T>::value), l, st,
+                hipLaunchKernelGGL((k_particles_cells<T, O, false>), dim3(ntiles), dim3(TileThreads<T, O>::value), l, st,
                                    pc, tq, in, out, f, tile_start, stray, g, f0s, kc, err);
             }
             return hipGetLastError();
         }
     } else {
-        (void)scratch;
         (void)attr_cp;
         (void)attr_cg;
     }
     const size_t lds = tile_lds_bytes<T>(O, tg);
-    if (g.flag_next) {
-        allow_big_lds(&k_particles_tile<T, O, true>, attr_guests);
-        hipLaunchKernelGGL((k_particles_tile<T, O, true>), dim3(ntiles), dim3(TileThreads<T>::value), lds, st, pc, tg,
-                           in, out, f, tile_start, stray, g, err);
+    auto launch = [&](auto *kernel, bool &attr, int nth) {
+        allow_big_lds(kernel, attr);
+        hipLaunchKernelGGL(kernel, dim3(ntiles), dim3(nth), lds, st, pc, tg, in, out, f, tile_start, stray, g, f0s,
+                           err);
+    };
+    constexpr int most = TileThreads<T, O>::value;
+    // Every wave stages and flushes, but tiles of few particles end sooner
+    // with fewer waves of more registers: FP64 at 512 / 768 threads, 128^3, 8
+    // per cell (2048 per tile) 3.25 / 3.19 ms a step; 16^3, 2 per cell (128)
+    // 15.6 / 16.8 us.
+    if (most > 512 && sizeof(T) == 8 && in.n <= (int64_t)512 * ntiles) {
+        if (g.flag_next)
+            launch(&k_particles_tile<T, O, true, 512>, attr_few_guests, 512);
+        else
+            launch(&k_particles_tile<T, O, false, 512>, attr_few, 512);
+    } else if (g.flag_next) {
+        launch(&k_particles_tile<T, O, true, most>, attr_guests, most);
     } else {
-        allow_big_lds(&k_particles_tile<T, O, false>, attr_plain);
-        hipLaunchKernelGGL((k_particles_tile<T, O, false>), dim3(ntiles), dim3(TileThreads<T>::value), lds, st, pc,
-                           tg, in, out, f, tile_start, stray, g, err);
+        launch(&k_particles_tile<T, O, false, most>, attr_plain, most);
     }
     return hipGetLastError();
 }

@@ -228,6 +228,53 @@ __device__ __attribute__((always_inline)) inline void region_walk(const int *n, 
     region_cells(n, t0, lo, ex, ey, ez, once, [&](int x, int y, int z, int gi) { fn(x + px * (y + ey * z), gi); });
 }
 
+// A tile region's values of NV fields copied by the whole workgroup:
+// load(global index, v) reads them, store(x, y, z, v) puts them down.  R rows
+// per thread are requested before the first is stored, with no branch between
+// the loads (a lane or row past the region reads its last value and stores
+// nothing): a branch there makes a wave wait out the memory latency at each
+// row, with the values in scratch.
+template <int R, int NV, typename V, typename LoadFn, typename StoreFn>
+__device__ __attribute__((always_inline)) inline void region_stage(const int *n, const int *t0, int lo, int ex,
+                                                                    int ey, int ez, bool once, LoadFn &&load,
+                                                                    StoreFn &&store)
+{
+    if (once) {
+        const int lb = ex > 1 ? 32 - __clz(ex - 1) : 0;
+        const int x = (int)threadIdx.x & ((1 << lb) - 1), step = (int)blockDim.x >> lb;
+        const int gx = wrap_once(t0[0] - lo + (x < ex ? x : ex - 1), n[0]);
+        int y = ((int)threadIdx.x >> lb) % ey, z = ((int)threadIdx.x >> lb) / ey;
+        const int sy = step % ey, sz = step / ey;
+        for (int r = 0; r < ey * ez; r += R * step) {
+            V v[R][NV];
+            int ay[R], az[R];
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+                const int gy = wrap_once(t0[1] - lo + y, n[1]);
+                const int gz = wrap_once(t0[2] - lo + (z < ez ? z : ez - 1), n[2]);
+                load(gx + n[0] * (gy + n[1] * gz), v[t]);
+                ay[t] = y;
+                az[t] = z;
+                y += sy;
+                z += sz;
+                const bool over = y >= ey;
+                y -= over ? ey : 0;
+                z += over ? 1 : 0;
+            }
+#pragma unroll
+            for (int t = 0; t < R; ++t)
+                if (x < ex && az[t] < ez)
+                    store(x, ay[t], az[t], v[t]);
+        }
+    } else {
+        region_cells(n, t0, lo, ex, ey, ez, false, [&](int x, int y, int z, int gi) {
+            V v[NV];
+            load(gi, v);
+            store(x, y, z, v);
+        });
+    }
+}
+
 // true when the region of extents e starting lo cells below a tile of
 // extents t wraps each axis of the grid at most once (wrap_once suffices)
 __device__ inline bool region_wraps_once(const int *n, const int *t, int lo, const int *e)
@@ -237,6 +284,40 @@ __device__ inline bool region_wraps_once(const int *n, const int *t, int lo, con
     for (int d = 0; d < 3; ++d)
         ok = ok && lo <= n[d] && e[d] - t[d] - lo <= n[d];
     return ok;
+}
+
+// E and B of a tile's field region into LDS: component m of (x, y, z) at
+// sF[m * pm + x + py * y + pz * z].  R rows per thread at a time (first-order
+// regions have hardly more rows than a workgroup takes at once).
+template <int R, typename T>
+__device__ __attribute__((always_inline)) inline void stage_fields(const FieldPtrs<T> &fp, const int *n,
+                                                                    const TileGeo &tg, const int *t0, T *sF, int pm,
+                                                                    int py, int pz)
+{
+    region_stage<R, 6, T>(
+        n, t0, tg.lo_f, tg.rf[0], tg.rf[1], tg.rf[2], region_wraps_once(n, tg.t, tg.lo_f, tg.rf),
+        [&](int gi, T *v) {
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+                v[m] = fp.E[m][gi];
+                v[3 + m] = fp.B[m][gi];
+            }
+        },
+        [&](int x, int y, int z, const T *v) {
+            T *s = sF + x + py * y + pz * z;
+#pragma unroll
+            for (int m = 0; m < 6; ++m)
+                s[m * pm] = v[m];
+        });
+}
+
+// An index into rows of 16 values, the halves of every second row exchanged:
+// sixteen lanes that add to eight cells of two neighbouring rows then fall on
+// all the LDS banks, as they would not at any pitch below 24.  fold is 8, or
+// 0 for rows of another pitch.
+__device__ inline int lds_fold(int i, int fold)
+{
+    return i ^ ((i >> 1) & fold);
 }
 
 // A list of strays on the device, appended to by the tile kernels (one
@@ -284,7 +365,8 @@ __device__ __attribute__((always_inline)) inline void deposit_local_comp(const P
         K[d] = pc.jk[d] * w;
         axis_offsets_local<NW + 1>(l[d] + lo_j, e[d].lo, sj[d], jo[d]);
     }
-    esk_scatter<O, T, double, M>(e, jo, K, [&](int, int idx, double v) { latomic_add(sA + idx, v); });
+    const int *const jx[2] = {jo[0], jo[0]};
+    esk_scatter<O, T, double, M>(e, jo, jx, K, [&](int, int idx, double v) { latomic_add(sA + idx, v); });
 }
 
 // Esirkepov full-window current straight into global memory (a crosser
@@ -305,7 +387,8 @@ __device__ __attribute__((always_inline)) inline void deposit_global_full(const 
         K[d] = pc.jk[d] * w;
         axis_offsets_global<NW + 1>(c[d], e[d].lo, pc.n[d], gs[d], jo[d]);
     }
-    esk_scatter<O, T, T>(e, jo, K, [&](int m, int idx, T v) { gatomic_add(fp.J[m] + idx, v); });
+    const int *const jx[2] = {jo[0], jo[0]};
+    esk_scatter<O, T, T>(e, jo, jx, K, [&](int m, int idx, T v) { gatomic_add(fp.J[m] + idx, v); });
 }
 
 }  // namespace pic

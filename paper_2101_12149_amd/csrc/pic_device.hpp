@@ -92,14 +92,11 @@ __device__ inline void axis_weights(T f, AxisW<O, T> &a)
     using S = Shape<O, T>;
     S::w(f, a.wn);
     a.bn = S::NB;
-    // staggered sample points sit at node + 1/2: coordinate f - 1/2
-    if (f >= T(0.5)) {
-        S::w(f - T(0.5), a.ws);
-        a.bs = S::NB;
-    } else {
-        S::w(f + T(0.5), a.ws);
-        a.bs = S::NB - 1;
-    }
+    // staggered sample points sit at node + 1/2: coordinate f - 1/2 (without a
+    // branch: a wave's particles sit in both halves of their cells)
+    const bool up = f >= T(0.5);
+    S::w(up ? f - T(0.5) : f + T(0.5), a.ws);
+    a.bs = up ? S::NB : S::NB - 1;
 }
 
 template <int O, typename T>
@@ -107,10 +104,7 @@ __device__ inline void axis_dweights(T f, T *dn, T *ds)
 {
     using S = Shape<O, T>;
     S::dw(f, dn);
-    if (f >= T(0.5))
-        S::dw(f - T(0.5), ds);
-    else
-        S::dw(f + T(0.5), ds);
+    S::dw(f >= T(0.5) ? f - T(0.5) : f + T(0.5), ds);
 }
 
 // sum_k wz[k] sum_j wy[j] sum_i wx[i] F[xo[i] + yo[j] + zo[k]]
@@ -502,11 +496,12 @@ __device__ inline void esk_axis_deriv(T d0, T d1, int kappa, T *dS0, T *dDS1)
 // accumulator type A (double for the LDS current tile, whose FP64 atomics
 // are far faster than FP32 ones on gfx950).  `add(m, index, value)`
 // performs the scatter; jo[d][a] are the index offsets of window node a
-// along axis d.
+// along axis d, and jx[k][a] those along x in rows whose y and z nodes add up
+// to an even (k = 0) or odd number: jo[0] twice unless the rows are folded.
 // With MSEL in 0..2 only that component is scattered.
 template <int O, typename T, typename A, int MSEL = -1, typename AddFn>
-__device__ __attribute__((always_inline)) inline void esk_scatter(const EskAxis<O, T> *e, const int (*jo)[Shape<O, T>::NW + 1], const T *K,
-                                   AddFn &&add)
+__device__ __attribute__((always_inline)) inline void esk_scatter(const EskAxis<O, T> *e, const int (*jo)[Shape<O, T>::NW + 1],
+                                   const int *const *jx, const T *K, AddFn &&add)
 {
     constexpr int NW = Shape<O, T>::NW;
     const T half = T(0.5), third = T(1) / T(3);
@@ -535,12 +530,14 @@ __device__ __attribute__((always_inline)) inline void esk_scatter(const EskAxis<
                     continue;
                 const A C = (A)(e[p].S0[b] * (e[q].S0[c] + half * e[q].DS[c]) +
                                 e[p].DS[b] * (half * e[q].S0[c] + third * e[q].DS[c]));
-                const int base = jo[p][b] + jo[q][c];
 #pragma unroll
                 for (int a = 0; a < NW; ++a) {
                     if (a == NW - 1 && !xm)
                         continue;
-                    add(m, base + jo[m][a], P[a] * C);
+                    const int i = m == 0   ? jo[1][b] + jo[2][c] + jx[(b + c) & 1][a]
+                                  : m == 1 ? jo[2][b] + jx[(a + b) & 1][c] + jo[1][a]
+                                           : jx[(a + c) & 1][b] + jo[1][c] + jo[2][a];
+                    add(m, i, P[a] * C);
                 }
             }
         }

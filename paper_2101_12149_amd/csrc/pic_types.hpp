@@ -46,10 +46,21 @@ struct TileGeo {
     int slack;
     int lo_f, rf[3];
     int lo_j, rj[3];
-    int jp;        // row pitch of the forward kernel's LDS current tile (>= rj[0])
+    int jp;        // row pitch of an unpadded current tile in LDS (rj[0])
+    // the one-pass tile kernel's: pitch of a row of six field components and
+    // of a plane, pitch of a row of a current component, and its lds_fold
+    int pr, ps, jq, fold;
     int xcd_map;   // spread consecutive tiles so each XCD gets a contiguous block
     int qcap;      // entries of the tile kernel's LDS queue of cell-crossing particles
+    int qoff;      // the queue holds their offsets too
 };
+
+// values of the one-pass tile kernel's three current components: J_z ends one
+// plane earlier
+__host__ __device__ inline int tile_current_values(const TileGeo &tg)
+{
+    return tg.jq * tg.rj[1] * (3 * tg.rj[2] - 1);
+}
 
 // Arguments of the curl-update kernel:
 //   out = in + (cx,cy,cz)-weighted curl(src)  [forward or backward differences]

@@ -746,6 +746,40 @@ def test_f32_order3_particles_that_end_at_a_cell_face(ppc):
     assert rel_l2(_cpu(gf.J), of.J) < 1e-5
 
 
+@pytest.mark.parametrize("tile, slack", [
+    ((8, 8, 4), 1),    # folded current rows, offsets of the crossers in memory
+    ((8, 7, 4), 1),    # an even number of current rows: not folded
+    ((4, 4, 4), 1),    # the queue holds the offsets
+    ((5, 6, 3), 2),
+    ((7, 8, 5), 1),    # regions that leave no room for padding in FP64
+    ((16, 4, 2), 0),
+])
+@pytest.mark.parametrize("order", [1, 3])
+@pytest.mark.parametrize("dtype, ppc", [("f64", 2), ("f64", 9), ("f32", 9)])
+def test_one_pass_tile_kernel_layouts_match_oracle(dtype, ppc, order, tile, slack):
+    """The tile kernel's LDS layouts and workgroup sizes, in place on a hot
+    plasma (u_th = 0.4c: the queue of cell-changing particles overflows on
+    some), two steps without a sort in between.  FP64 within 1e-12, particle
+    by particle; FP32 within rel-L2 1e-5 per step for the fields."""
+    n = tuple(2 * t if t > 4 else 4 * t for t in tile)
+    g = wl.plasma_grid(n, order)
+    g.tile, g.slack = tile, slack
+    npart = ppc * n[0] * n[1] * n[2]
+    sp = dev(random_species(g, npart, 161, u_th=0.4, dtype=dtype))
+    ts = torch.zeros(_lib.pic_tile_count(g, dtype) + 1, dtype=torch.int32, device="cuda")
+    _lib.pic_sort_tiles(g, sp, ts, _lib.workspace(g, dtype, npart))
+    w = wl.Workload("layout", g, sp.to(device="cpu"), random_fields(g, 162, scale=0.05, dtype=dtype), None, 2, 0,
+                    dtype, 161)
+    gsp, gf, _ = _run_gpu_steps(w, 2, 0, tile_start=ts)
+    osp, of, _ = _run_oracle(w, 2)
+    tol = F64_TOL if dtype == "f64" else 2e-5
+    for name in ("E", "B", "J"):
+        assert rel_l2(_cpu(getattr(gf, name)), getattr(of, name)) < tol, name
+    if dtype == "f64":
+        assert np.array_equal(gsp.cell.cpu().numpy(), osp.cell)
+        assert max_rel(_cpu(gsp.u), osp.u) < F64_TOL
+
+
 def test_guest_lists_overflow_to_the_stray_path():
     """64 ppc at u_th = 0.9c on 16^3, sorted once and then stepped without
     re-sorting: thousands of particles per tile leave their home region each
