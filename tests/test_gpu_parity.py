@@ -337,6 +337,62 @@ def test_sort_tiles_is_a_binning_permutation():
     assert np.array_equal(ts.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("order", ["random", "loops", "drifted"])
+@pytest.mark.parametrize("n, dtype, weights", [((48, 40, 56), "f64", True), ((8, 8, 4), "f32", False),
+                                               ((35, 28, 20), "f32", True)])
+def test_sort_of_a_large_species_in_any_order(n, dtype, weights, order):
+    """A species large enough for the passes that count and scatter through
+    LDS, with a ragged last segment: a permutation, rank-major inside every
+    tile, the particles' data moved with it; from a random order, from the
+    loops over a grid's cells and from an earlier sort's order after a drift
+    of a cell, and on a grid smaller than the counting region."""
+    g = wl.plasma_grid(n, 3)
+    npart = (1 << 21) + 777
+    gen = torch.Generator(device="cuda").manual_seed(171)
+    if order == "random":
+        cell = torch.stack([torch.randint(0, m, (npart,), generator=gen, device="cuda") for m in n])
+    else:
+        lin = torch.arange(npart, device="cuda") * (n[0] * n[1] * n[2]) // npart
+        cell = torch.stack([lin % n[0], lin // n[0] % n[1], lin // (n[0] * n[1])])
+    real = tdtype(dtype)
+    sp = wl.Species(cell.to(torch.int32).contiguous(),
+                    torch.rand((3, npart), generator=gen, device="cuda", dtype=real).clamp(max=0.999),
+                    torch.randn((3, npart), generator=gen, device="cuda", dtype=real),
+                    torch.rand(npart, generator=gen, device="cuda", dtype=real) if weights else None, 1.0)
+    nt = _lib.pic_tile_count(g, dtype)
+    ts = torch.empty(nt + 1, dtype=torch.int32, device="cuda")
+    ws = _lib.workspace(g, dtype, npart)
+    if order == "drifted":
+        _lib.pic_sort_tiles(g, sp, ts, ws)
+        step = torch.randint(-1, 2, (3, npart), generator=gen, device="cuda", dtype=torch.int32)
+        sp.cell = torch.remainder(sp.cell + step, torch.tensor(n, device="cuda")[:, None]).to(torch.int32).contiguous()
+    d = sp.clone()
+    perm = torch.empty(npart, dtype=torch.int32, device="cuda")
+    _lib.pic_sort_tiles(g, d, ts, ws, perm=perm)
+    torch.cuda.synchronize()
+    p = perm.long()
+    assert torch.equal(torch.sort(p)[0], torch.arange(npart, device="cuda"))
+    for a, b in ((d.cell, sp.cell), (d.off, sp.off), (d.u, sp.u)):
+        assert torch.equal(a, b[:, p])
+    if weights:
+        assert torch.equal(d.w, sp.w[p])
+    (tx, ty, tz), _ = _lib.pic_tile_shape(g, dtype)
+    c = d.cell.long()
+    tile = (c[0] // tx) + (n[0] // tx) * ((c[1] // ty) + (n[1] // ty) * (c[2] // tz))
+    local = (c[0] % tx) + tx * ((c[1] % ty) + ty * (c[2] % tz))
+    want = torch.cat([torch.zeros(1, dtype=torch.long, device="cuda"), torch.cumsum(torch.bincount(tile, minlength=nt), 0)])
+    assert torch.equal(ts.long(), want)
+    assert bool((tile[1:] >= tile[:-1]).all())
+    # occurrence of the particle's cell so far: its place among the cell's
+    key = tile * (tx * ty * tz) + local
+    by_cell = torch.argsort(key, stable=True)
+    first = torch.cumsum(torch.bincount(key), 0) - torch.bincount(key)
+    occ = torch.empty_like(key)
+    occ[by_cell] = torch.arange(npart, device="cuda") - first[key[by_cell]]
+    place = (tile << 42) + (occ << 12) + local
+    assert bool((place[1:] > place[:-1]).all())
+
+
 def test_sort_rejects_corrupt_state_without_touching_it():
     g = wl.plasma_grid((16, 16, 16), 3)
     sp = random_species(g, 1000, 62, dtype="f64")
