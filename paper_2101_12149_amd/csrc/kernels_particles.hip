@@ -2312,17 +2312,16 @@ __global__ void __launch_bounds__(NTH) k_adjoint_push_tile(PConst<T> pc, TileGeo
                                                                            StrayList strays, int *crossq, int *err)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int rfx = tg.rf[0], rfy = tg.rf[1];
-    const int rfvol = rfx * rfy * tg.rf[2];
-    const int rjx = tg.rj[0], rjy = tg.rj[1];
-    const int rjvol = rjx * rjy * tg.rj[2];
-    T *sF = reinterpret_cast<T *>(smem_raw);   // 6 * rfvol
-    T *sH = sF + 6 * rfvol;                    // 3 * rjvol
+    // rows of six field components, of three components of hatE
+    const int rjx = tg.rj[0], rjy = tg.rj[1], hs = tg.jq * rjy;
+    T *sF = reinterpret_cast<T *>(smem_raw);
+    T *sH = sF + tg.ps * tg.rf[2];
+    T *sT = sH + hs * tg.rj[2];   // the stash
     const TileSpan ts = tile_span(tg, tile_start, sp.n);
     if (ts.pe <= ts.ps)
         return;   // uniform across the workgroup
     const int tid = threadIdx.x, nth = blockDim.x;
-    stage_fields<O == 1 ? 1 : sizeof(T) == 4 ? 4 : 2>(fp, pc.n, tg, ts.t0, sF, rfvol, rfx, rfx * rfy);
+    stage_fields<O == 1 ? 1 : sizeof(T) == 4 ? 4 : 2>(fp, pc.n, tg, ts.t0, sF, tg.rf[0], tg.pr, tg.ps);
     region_stage<sizeof(T) == 4 ? 4 : 2, 3, T>(
         pc.n, ts.t0, tg.lo_j, rjx, rjy, tg.rj[2], region_wraps_once(pc.n, tg.t, tg.lo_j, tg.rj),
         [&](int gi, T *v) {
@@ -2333,24 +2332,24 @@ __global__ void __launch_bounds__(NTH) k_adjoint_push_tile(PConst<T> pc, TileGeo
         [&](int x, int y, int z, const T *v) {
 #pragma unroll
             for (int m = 0; m < 3; ++m)
-                sH[m * rjvol + x + rjx * (y + rjy * z)] = v[m];
+                sH[m * rjx + x + tg.jq * y + hs * z] = v[m];
         });
     __syncthreads();
     FieldSrc<T> lf;
 #pragma unroll
     for (int m = 0; m < 6; ++m)
-        lf.c[m] = sF + m * rfvol;
-    const T *lh[3] = {sH, sH + rjvol, sH + 2 * rjvol};
-    const int sf[3] = {1, rfx, rfx * rfy};
-    const int sj[3] = {1, rjx, rjx * rjy};
+        lf.c[m] = sF + m * tg.rf[0];
+    const T *lh[3] = {sH, sH + rjx, sH + 2 * rjx};
+    const int sf[3] = {1, tg.pr, tg.ps};
+    const int sj[3] = {1, tg.jq, hs};
     const int np = (int)(ts.pe - ts.ps);
     // the count of the tile's cell-changing particles, after the stash
-    int *ncross = reinterpret_cast<int *>(sH + 3 * rjvol + (STASH ? 18 * NTH : 0));
+    int *ncross = reinterpret_cast<int *>(sT + (STASH ? 18 * NTH : 0));
     if (tid == 0)
         *ncross = 0;
     __syncthreads();
     const StrayList cross{crossq + ts.ps, ncross, np};
-    T *const stash = sH + 3 * rjvol + tid;
+    T *const stash = sT + tid;
     for (int j0 = 0; j0 < np; j0 += nth) {
         const int j = j0 + tid;
         bool stray = false, crosser = false;
@@ -3013,6 +3012,33 @@ size_t adjoint_push_lds(const TileGeo &tg)
     return 6 * rf * sizeof(T) + 3 * rj * sizeof(T) + 16;   // and the count of cell-changing particles
 }
 
+// The same with rows padded so that eight cells of neighbouring rows fall on
+// different banks (as the forward tile kernel's), as far as the LDS has room
+// beside `more` bytes: the fields' rows, then hatE's too.  Returns the bytes
+// taken, 0 if not even the unpadded regions fit.  (With the staging of several
+// rows at a time, a laser box of 2 per cell 6.9 -> 6.2 ms for the pass; at 8
+// per cell the gradients leave no room, and fewer threads to make some cost
+// more: 128^3, the whole reverse step, 3.58 ms at 768, 3.71 at 704 with it.)
+template <typename T>
+static size_t adjoint_push_layout(TileGeo &tg, size_t more)
+{
+    const int banks = 128 / (int)sizeof(T), t0 = tg.t[0] % banks;
+    auto pitch = [&](int p, bool pad) {
+        while (pad && p % banks != t0 && p % banks != banks - t0)
+            ++p;
+        return p;
+    };
+    for (int pad = 2; pad >= 0; --pad) {
+        tg.pr = pitch(6 * tg.rf[0], pad > 0);
+        tg.ps = tg.pr * tg.rf[1];
+        tg.jq = pitch(3 * tg.rj[0], pad > 1);
+        const size_t l = ((size_t)tg.ps * tg.rf[2] + (size_t)tg.jq * tg.rj[1] * tg.rj[2]) * sizeof(T) + 16 + more;
+        if (l <= 160 * 1024)
+            return l;
+    }
+    return 0;
+}
+
 // dynamic LDS one workgroup of the tiled adjoint scatter may take
 constexpr size_t ADJ_QUEUE_LDS = 160 * 1024;
 
@@ -3088,7 +3114,7 @@ static hipError_t launch_adj_tile_o(const PConst<T> &pc, const TileGeo &tg, cons
     allow_big_lds(&k_adjoint_scatter_tile<T, O>, a2);
     const unsigned ntiles = (unsigned)(tg.nt[0] * tg.nt[1] * tg.nt[2]);
     const unsigned nth = AdjThreads<T>::value;
-    const size_t l1 = adjoint_push_lds<T>(tg), l2 = adjoint_scatter_lds<T>(tg);
+    const size_t l2 = adjoint_scatter_lds<T>(tg);
     // the LDS the accumulators leave holds the scatter's queue (16 bytes of
     // counter, then 4 per entry, up to 16384)
     const size_t room = l2 + 16 < ADJ_QUEUE_LDS ? (ADJ_QUEUE_LDS - l2 - 16) / 4 : 0;
@@ -3107,32 +3133,35 @@ static hipError_t launch_adj_tile_o(const PConst<T> &pc, const TileGeo &tg, cons
         // the gradient stash: 18 values per thread after the field regions
         static bool s1 = false, s1d = false;
         const int nt = dense ? PushThreads<T>::dense : PushThreads<T>::value;
-        const size_t ls = l1 + 18 * sizeof(T) * (size_t)nt;
-        if (ls <= 160 * 1024) {
+        TileGeo tp = tg;
+        const size_t ls = adjoint_push_layout<T>(tp, 18 * sizeof(T) * (size_t)nt);
+        if (ls > 0) {
             if (dense) {
                 allow_big_lds(&k_adjoint_push_tile<T, O, PushThreads<T>::dense, true, true>, s1d);
                 hipLaunchKernelGGL((k_adjoint_push_tile<T, O, PushThreads<T>::dense, true, true>), dim3(ntiles),
-                                   dim3(PushThreads<T>::dense), ls, st, pc, tg, sp, f, ap, tile_start, sl, crossq, err);
+                                   dim3(PushThreads<T>::dense), ls, st, pc, tp, sp, f, ap, tile_start, sl, crossq, err);
             } else if (split_sparse) {
                 static bool s1s = false;
                 allow_big_lds(&k_adjoint_push_tile<T, O, PushThreads<T>::value, true, true>, s1s);
                 hipLaunchKernelGGL((k_adjoint_push_tile<T, O, PushThreads<T>::value, true, true>), dim3(ntiles),
-                                   dim3(PushThreads<T>::value), ls, st, pc, tg, sp, f, ap, tile_start, sl, crossq, err);
+                                   dim3(PushThreads<T>::value), ls, st, pc, tp, sp, f, ap, tile_start, sl, crossq, err);
             } else {
                 allow_big_lds(&k_adjoint_push_tile<T, O, PushThreads<T>::value, true, false>, s1);
                 hipLaunchKernelGGL((k_adjoint_push_tile<T, O, PushThreads<T>::value, true, false>), dim3(ntiles),
-                                   dim3(PushThreads<T>::value), ls, st, pc, tg, sp, f, ap, tile_start, sl, crossq, err);
+                                   dim3(PushThreads<T>::value), ls, st, pc, tp, sp, f, ap, tile_start, sl, crossq, err);
             }
             stashed = true;
         }
     }
     if (!stashed) {
+        TileGeo tp = tg;
+        const size_t ls = adjoint_push_layout<T>(tp, 0);
         if (dense)
             hipLaunchKernelGGL((k_adjoint_push_tile<T, O, PushThreads<T>::dense, false, true>), dim3(ntiles),
-                               dim3(PushThreads<T>::dense), l1, st, pc, tg, sp, f, ap, tile_start, sl, crossq, err);
+                               dim3(PushThreads<T>::dense), ls, st, pc, tp, sp, f, ap, tile_start, sl, crossq, err);
         else
             hipLaunchKernelGGL((k_adjoint_push_tile<T, O, PushThreads<T>::value, false, false>), dim3(ntiles),
-                               dim3(PushThreads<T>::value), l1, st, pc, tg, sp, f, ap, tile_start, sl, crossq, err);
+                               dim3(PushThreads<T>::value), ls, st, pc, tp, sp, f, ap, tile_start, sl, crossq, err);
     }
     hipLaunchKernelGGL((k_adjoint_push_strays<T, O>), dim3(nsb), dim3(STRAY_THREADS), 0, st, pc, sp, f, ap, sl, err);
     bool cells = false;

@@ -229,6 +229,40 @@ def test_tiled_adjoint_on_dense_tiles_matches_oracle(order, dtype, layout):
         assert r < tol, (name, r)
 
 
+@pytest.mark.parametrize("tile, ppc, order, dtype", [
+    ((8, 8, 8), 8, 3, "f32"),    # little room beside the gradients: rows unpadded
+    ((8, 8, 8), 2, 3, "f32"),    # the fields' and hatE's rows padded
+    ((8, 8, 7), 8, 3, "f32"),    # the fields' only
+    ((5, 6, 7), 8, 3, "f32"),
+    ((4, 4, 4), 2, 3, "f32"),
+    ((8, 8, 8), 8, 1, "f64"),
+])
+def test_tiled_adjoint_over_tile_shapes_matches_oracle(tile, ppc, order, dtype):
+    """The reverse step's LDS layouts: random placement, tolerances of the
+    other tiled reverse steps."""
+    g = wl.plasma_grid(tuple(2 * t for t in tile), order)
+    g.tile = tile
+    sp = _dense_species(g, ppc, 311, dtype, "poisson")
+    n = sp.cell.shape[1]
+    f = random_fields(g, 312, scale=0.3, dtype=dtype)
+    lam = _random_lambda(g, n, 314, dtype)
+    dsp = dev(sp)
+    ws = _lib.workspace(g, dtype, n)
+    ts = torch.zeros(_lib.pic_tile_count(g, dtype) + 1, dtype=torch.int32, device="cuda")
+    perm = torch.empty(n, dtype=torch.int32, device="cuda")
+    _lib.pic_sort_tiles(g, dsp, ts, ws, perm=perm)
+    pl = perm.cpu().long()
+    lam.lx, lam.lu = lam.lx[:, pl].contiguous(), lam.lu[:, pl].contiguous()
+    olam = _oracle_lambda(lam)
+    dlam = NS(lx=dev(lam.lx), lu=dev(lam.lu), lE=dev(lam.lE), lB=dev(lam.lB))
+    _lib.pic_step_adjoint(g, dsp, dev(f), None, 2, dlam, None, ws, tile_start=ts)
+    torch.cuda.synchronize()
+    oracle.step_adjoint(g, dsp.to(device="cpu").numpy(), f.numpy(), None, 2, olam, None)
+    tol = 1e-12 if dtype == "f64" else 1e-4
+    for name in ("lx", "lu", "lE", "lB"):
+        assert rel_l2(_cpu(getattr(dlam, name)), getattr(olam, name)) < tol, name
+
+
 @pytest.mark.parametrize("tiled", [False, True])
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 def test_adjoint_on_the_smallest_grid_with_every_option(dtype, tiled):
