@@ -853,9 +853,13 @@ pic_status step_t(const pic_grid *g, const GridInfo &gi, pic_species *sp, pic_fi
     for (int d = 0; d < 3; ++d)
         bh[d] = reinterpret_cast<T *>(w + L.hatE + d * al(sizeof(T) * (size_t)gi.ncell));
     const bool chain = g->solver == PIC_SOLVER_YEE;
-    PIC_HIP(launch_fill<int>(err, 1, 0, st));
+    // cleared before the first step, and the counters again before each
+    ClearList clear;
+    clear.add(err, 1);
     for (int d = 0; d < 3; ++d)
-        PIC_HIP(launch_fill<T>(fp.J[d], gi.ncell, T(0), st));
+        clear.add(fp.J[d], gi.ncell);
+    if (nsteps < 1)
+        PIC_HIP(launch_clear(clear, st));
     for (int32_t it = 0; it < nsteps; ++it) {
         const int64_t step = step0 + it;
         const bool sort_now = sort_every > 0 && (it == 0 || step % sort_every == 0);
@@ -876,9 +880,15 @@ pic_status step_t(const pic_grid *g, const GridInfo &gi, pic_species *sp, pic_fi
             ga.list_next = glist[nxt];
             ga.flag_next = gflag[nxt];
             ga.cap = GUEST_CAP;
-            if (tile_start && sp->n > 0)
-                PIC_HIP(launch_fill<int>(ga.cnt_next, gi.ntiles, 0, st));
         }
+        // the tile kernel appends to the strays and the next guest lists
+        if (tile_start && sp->n > 0) {
+            clear.add(stray_cnt, 1);
+            if (ga.cnt_next)
+                clear.add(ga.cnt_next, gi.ntiles);
+        }
+        PIC_HIP(launch_clear(clear, st));
+        clear.count = 0;
         if (sort_now && sp->n > 0) {
             PArr<T> sorted;
             {

@@ -2850,9 +2850,6 @@ hipError_t launch_particles_tile(int order, const PConst<T> &pc, const TileGeo &
                                  hipStream_t st)
 {
     const StrayList sl{stray_list, stray_cnt, (int)in.n};
-    const hipError_t e0 = launch_fill<int>(stray_cnt, 1, 0, st);
-    if (e0 != hipSuccess)
-        return e0;
     return order == 1 ? launch_tile_o<T, 1>(pc, tg, in, out, f, tile_start, sl, g, scratch, err, st)
                       : launch_tile_o<T, 3>(pc, tg, in, out, f, tile_start, sl, g, scratch, err, st);
 }

@@ -107,7 +107,7 @@ struct GuestArgs {
 // ---------------------------------------------------------------------------
 // launchers (return hipSuccess or the launch error)
 
-// stray_list (int[n]) and stray_cnt (one int, cleared by the launcher):
+// stray_list (int[n]) and stray_cnt (one int, cleared by the caller):
 // the particles the tile kernel leaves to the stray kernel; scratch: three
 // T[n] arrays that hold old offsets between the two-phase kernel's phases
 // when in and out are the same arrays
@@ -182,6 +182,20 @@ template <typename T>
 hipError_t launch_filter_z(const T *in, T *out, const T w[4], bool add, const int n[3], hipStream_t st);
 template <typename T>
 hipError_t launch_fill(T *p, int64_t n, T v, hipStream_t st);
+
+// arrays of n 4-byte words to clear
+struct ClearList {
+    int count = 0;
+    int *p[6];
+    int64_t n[6];
+    template <typename V>
+    void add(V *q, int64_t values)
+    {
+        p[count] = reinterpret_cast<int *>(q);
+        n[count++] = values * (int64_t)(sizeof(V) / sizeof(int));
+    }
+};
+hipError_t launch_clear(const ClearList &c, hipStream_t st);
 template <typename T>
 hipError_t launch_scale(T *out, const T *in, int64_t n, T a, hipStream_t st);
 hipError_t launch_sum2(const double *in, double *out, hipStream_t st);
