@@ -318,21 +318,25 @@ static unsigned seg_blocks(int64_t n, int per_block)
 // at a quarter of the rate that its loads and stores reach; but input mostly
 // has an order (an earlier sort's that was drifted out of, or the loops of
 // what set the particles up).  A workgroup therefore counts its consecutive
-// particles in LDS over the cells near the middle one's tile (SEG_MARGIN cells
-// around it, along x the neighbouring tiles too; more of them gave nothing at
-// 2 per cell) and reserves each cell's range with one global atomic; particles
-// elsewhere take one each.  With the scatter below, a call's first sort:
-// 256^3, 8 per cell 8.1 -> 4.3 ms; 512^3, 2 per cell 19.9 -> 11.2 ms; 128^3, 8
-// per cell, FP64 1.43 -> 0.79 ms; 2^24 particles in random order 5.8 ms as
+// particles in LDS over the box of cells that they touch, or where that is too
+// large (some sit far from the others) over the cells near the middle one's
+// tile (SEG_MARGIN cells around it, along x the neighbouring tiles too; more
+// of them gave nothing at 2 per cell), and reserves each cell's range with one
+// global atomic; particles elsewhere take one each.  With the scatter below, a
+// call's first sort: 256^3, 8 per cell 8.1 -> 4.3 ms; 512^3, 2 per cell 19.9 ->
+// 11.5 ms; 128^3, 8 per cell, FP64 1.43 -> 0.79 ms; pic_sort_tiles of 2^26
+// particles listed cell by cell along x 11.1 -> 3.7 ms (9.1 with the tile's
+// region alone, which holds few of them); 2^24 in random order 5.7 ms as
 // before.
 static constexpr int SEG_MARGIN = 2;
+static constexpr int SEG_CELLS = 8192;   // cells of a box, at most
 
 template <typename T, int PER>
 __global__ void __launch_bounds__(SEG_T) k_bin_count(PArr<T> sp, TileGeo tg, int n0, int n1, int n2, int *counts,
                                                     int *key, int *rank, int *err)
 {
     extern __shared__ int lc[];
-    __shared__ int mid[3];
+    __shared__ int mid[3], lim[6];
     const int n[3] = {n0, n1, n2};
     const int64_t p0 = (int64_t)blockIdx.x * PER * blockDim.x + threadIdx.x;
     int c[PER][3];
@@ -360,29 +364,62 @@ __global__ void __launch_bounds__(SEG_T) k_bin_count(PArr<T> sp, TileGeo tg, int
     if (!ok)
         atomicOr(err, 1);
     // the region: origin o, extents e (each axis at most once around the grid)
-    int e[3], o[3];
+    int e[3] = {0, 0, 0}, o[3] = {0, 0, 0}, vol = 0;
+    if (PER > 1) {
+        if (threadIdx.x == 0) {
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const int most = (n[d] - tg.t[d]) / 2, want = SEG_MARGIN + (d == 0 ? tg.t[0] : 0);
-        const int m = want < most ? want : most;
-        e[d] = tg.t[d] + 2 * m;
-        o[d] = -m;
-    }
-    const int vol = PER > 1 ? e[0] * e[1] * e[2] : 0;
-    for (int r = threadIdx.x; r < vol; r += blockDim.x)
-        lc[r] = 0;
-    if (threadIdx.x == 0) {
+            for (int d = 0; d < 3; ++d)
+                mid[d] = c[PER / 2][d];
+        }
+        if (threadIdx.x < 6)
+            lim[threadIdx.x] = 0;   // least and largest distance from the middle one
+        __syncthreads();
+        int m[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            m[d] = mid[d];
+            int lo = 0, hi = 0;
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                int r = c[j][d] - m[d];
+                r = 2 * r < -n[d] ? r + n[d] : (2 * r >= n[d] ? r - n[d] : r);
+                lo = r < lo ? r : lo;
+                hi = r > hi ? r : hi;
+            }
+            for (int k = 32; k > 0; k >>= 1) {
+                const int x = __shfl_xor(lo, k, 64), y = __shfl_xor(hi, k, 64);
+                lo = x < lo ? x : lo;
+                hi = y > hi ? y : hi;
+            }
+            if ((threadIdx.x & 63) == 0) {
+                atomicMin(lim + d, lo);
+                atomicMax(lim + 3 + d, hi);
+            }
+        }
+        __syncthreads();
+        int64_t box = 1;
 #pragma unroll
         for (int d = 0; d < 3; ++d)
-            mid[d] = c[PER / 2][d] / tg.t[d] * tg.t[d];
-    }
-    __syncthreads();
-    int kk[PER], reg[PER], rk[PER];
+            box *= lim[3 + d] - lim[d] + 1;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        o[d] += mid[d];
-        o[d] = o[d] < 0 ? o[d] + n[d] : o[d];
+        for (int d = 0; d < 3; ++d) {
+            if (box <= SEG_CELLS) {
+                e[d] = lim[3 + d] - lim[d] + 1;
+                o[d] = m[d] + lim[d];
+            } else {
+                const int most = (n[d] - tg.t[d]) / 2, want = SEG_MARGIN + (d == 0 ? tg.t[0] : 0);
+                const int side = want < most ? want : most;
+                e[d] = tg.t[d] + 2 * side;
+                o[d] = m[d] / tg.t[d] * tg.t[d] - side;
+            }
+            o[d] = o[d] < 0 ? o[d] + n[d] : o[d];
+        }
+        vol = e[0] * e[1] * e[2];
+        for (int r = threadIdx.x; r < vol; r += blockDim.x)
+            lc[r] = 0;
+        __syncthreads();
     }
+    int kk[PER], reg[PER], rk[PER];
     const int tcells = tg.t[0] * tg.t[1] * tg.t[2];
     auto cell_key = [&](const int *v) {
         const int tx = v[0] / tg.t[0], ty = v[1] / tg.t[1], tz = v[2] / tg.t[2];
@@ -627,8 +664,8 @@ hipError_t launch_bin_count(const PArr<T> &sp, const TileGeo &tg, int *counts, i
                             hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
         attr = true;
     }
-    const size_t lds = sizeof(int) * (size_t)(3 * tg.t[0] + 2 * SEG_MARGIN) * (tg.t[1] + 2 * SEG_MARGIN) *
-                       (tg.t[2] + 2 * SEG_MARGIN);
+    const int near_tile = (3 * tg.t[0] + 2 * SEG_MARGIN) * (tg.t[1] + 2 * SEG_MARGIN) * (tg.t[2] + 2 * SEG_MARGIN);
+    const size_t lds = sizeof(int) * (size_t)(near_tile > SEG_CELLS ? near_tile : SEG_CELLS);
     hipLaunchKernelGGL((k_bin_count<T, SEG_PER>), dim3(seg_blocks(sp.n, SEG_T * SEG_PER)), dim3(SEG_T), lds, st, sp,
                        tg, n0, n1, n2, counts, key, rank, err);
     return hipGetLastError();
