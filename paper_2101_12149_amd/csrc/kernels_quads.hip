@@ -43,7 +43,6 @@ namespace {
 
 constexpr int QD_THREADS = 1024;   // threads of a workgroup, at most
 constexpr int QD_WAVES = QD_THREADS / 64;
-constexpr int QD_PER = 5;          // particles per thread and round, at most
 constexpr int QD_SLOTS = 4;        // cells (with the slack's) per thread, at most
 constexpr int QD_BATCH = 5;        // sparse tiles: batches of sixteen groups per wave and round
 constexpr int QD_MIN_ROUND = 256;  // particles of a round, at least
