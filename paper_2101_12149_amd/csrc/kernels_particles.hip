@@ -1732,7 +1732,7 @@ __device__ inline int box_rel(int c, int ref, int n)
 // after halving a part of it) fit a box whose region fits the LDS, the
 // fields of the box are staged there for the gather, or the current is
 // accumulated there in FP64 and flushed with one global atomic per non-zero
-// value.  Particles in any order are accepted: a segment of OPS_MIN
+// value.  Particles in any order are accepted: a segment of at most OPS_MIN
 // particles whose box does not fit runs on global memory.  There the deposit
 // is bound by its up to 300 global atomics per particle and the gather by
 // its 384 window reads through L1; in the LDS the deposit issues two atomics
@@ -1829,15 +1829,15 @@ __device__ inline CellBox segment_box(const PArr<T> &sp, const int *n, int64_t s
 }
 
 // region of a box with `halo` more nodes per axis; false where it does not
-// fit `room` values
-__device__ inline bool box_region(const CellBox &b, int halo, size_t room, int *ext)
+// fit `room` values or its rows the workgroup
+__device__ inline bool box_region(const CellBox &b, int halo, size_t room, int *ext, size_t &vol)
 {
-    size_t vol = 1;
+    vol = 1;
     bool ok = true;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         ext[d] = b.ext[d] + halo;
-        ok = ok && b.ext[d] <= OPS_MAX_EXT;
+        ok = ok && b.ext[d] <= OPS_MAX_EXT && ext[d] <= (int)blockDim.x;
         vol *= (size_t)ext[d];
     }
     return ok && vol <= room;
@@ -1859,6 +1859,50 @@ struct OpsThreads {
     static constexpr size_t gather_lds = sizeof(T) == 4 ? 80 * 1024 : 160 * 1024;
 };
 
+// Shortest segment that the gather halves to: below 512 particles a box pays
+// for the wide window in FP32 only (2.2 M listed cell by cell along x, 2 per
+// cell, at 512 / 256: FP32 737 / 486 us, FP64 811 / 1057 us).
+template <typename T, int O>
+__device__ constexpr int gather_min()
+{
+    return sizeof(T) == 4 && O == 3 ? OPS_MIN / 2 : OPS_MIN;
+}
+constexpr size_t OPS_NEAR = 16;
+
+// The gather of one particle per thread on global memory (first order; see
+// launch_gather_o for its range).
+template <typename T, int O>
+__global__ void __launch_bounds__(256) k_gather(PConst<T> pc, PArr<T> sp, FieldPtrs<T> fp, T *Ex, T *Ey, T *Ez,
+                                                T *Bx, T *By, T *Bz, int *err)
+{
+    constexpr int NW = Shape<O, T>::NW;
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= sp.n)
+        return;
+    int c[3];
+    T f[3], E[3] = {T(0), T(0), T(0)}, B[3] = {T(0), T(0), T(0)};
+    if (!load_position(sp, p, pc.n, c, f)) {
+        atomicOr(err, 1);
+    } else {
+        const int gs[3] = {1, pc.n[0], pc.n[0] * pc.n[1]};
+        AxisW<O, T> aw[3];
+        int on[3][NW], os[3][NW];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            axis_weights<O>(f[d], aw[d]);
+            axis_offsets_global<NW>(c[d], aw[d].bn, pc.n[d], gs[d], on[d]);
+            axis_offsets_global<NW>(c[d], aw[d].bs, pc.n[d], gs[d], os[d]);
+        }
+        gather_eb<O>(global_fields(fp), aw, on, os, E, B);
+    }
+    Ex[p] = E[0];
+    Ey[p] = E[1];
+    Ez[p] = E[2];
+    Bx[p] = B[0];
+    By[p] = B[1];
+    Bz[p] = B[2];
+}
+
 template <typename T, int O>
 __global__ void __launch_bounds__(OpsThreads<T>::gather) k_gather_box(PConst<T> pc, PArr<T> sp, FieldPtrs<T> fp,
                                                                      T *Ex, T *Ey, T *Ez, T *Bx, T *By, T *Bz,
@@ -1873,13 +1917,24 @@ __global__ void __launch_bounds__(OpsThreads<T>::gather) k_gather_box(PConst<T> 
     const int64_t end = base + chunk < sp.n ? base + chunk : sp.n;
     int len = chunk;
     for (int64_t s0 = base; s0 < end;) {
-        const int seg = (int)(end - s0 < len ? end - s0 : len);
+        int seg = (int)(end - s0 < len ? end - s0 : len);
         const CellBox b = segment_box(sp, pc.n, s0, seg, reinterpret_cast<int *>(smem_raw));
         int ext[3];
-        const bool fits = b.any && box_region(b, halo, (size_t)room, ext);
-        if (b.any && !fits && len > OPS_MIN) {
-            len >>= 1;   // uniform: every thread has the same box
-            continue;
+        size_t vol_box;
+        const bool fits = b.any && box_region(b, halo, (size_t)room, ext, vol_box);
+        if (b.any && !fits) {   // uniform: every thread has the same box
+            if (len > gather_min<T, O>()) {
+                len >>= 1;
+                continue;
+            }
+            // A box not much too large: the rest of the run is mostly in the
+            // same order (cell by cell along x on a wide grid) and is gathered
+            // from global memory without barriers, 2.2 M particles at 2 per
+            // cell, FP64 1057 -> 811 us.  Particles in no order keep the
+            // barriers, as fewer waves at a time thrash the caches less
+            // (2 M, FP64: 2.0 against 3.4 ms).
+            if (vol_box <= OPS_NEAR * (size_t)room)
+                seg = (int)(end - s0);
         }
         const int vol = fits ? ext[0] * ext[1] * ext[2] : 0;
         const int sf[3] = {1, ext[0], ext[0] * ext[1]};
@@ -1984,11 +2039,15 @@ __device__ inline bool load_move(const PArr<T> &b, const PArr<T> &a, int64_t p, 
 // lane per particle and component.  Where consecutive particles share a cell
 // (a load listed cell by cell) the lanes of a wave take particles seg /
 // blockDim.x apart, so that their atomics go to distinct addresses.
-template <typename T, int O>
+// With DIRECT (a run is one particle per thread) a workgroup whose
+// neighbours mostly sit in different cells deposits on global memory: in a
+// small first-order species the phases of the box take longer than its few
+// dozen atomics per particle (32 K binned particles: 75.8 us a call with the
+// box, 71 without; listed cell by cell, 8 per cell, 74 and 101).
+template <typename T, int O, bool DIRECT>
 __global__ void __launch_bounds__(OpsThreads<T>::deposit) k_deposit_box(PConst<T> pc, PArr<T> b, PArr<T> a,
                                                                        FieldPtrs<T> fp, int chunk, int room, int *err)
 {
-    constexpr int NW = Shape<O, T>::NW;
     constexpr int lo = O == 3 ? 2 : 1;     // nodes below the box
     constexpr int halo = O == 3 ? 5 : 3;   // on both sides together
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1998,12 +2057,38 @@ __global__ void __launch_bounds__(OpsThreads<T>::deposit) k_deposit_box(PConst<T
     const int tid = threadIdx.x, nth = blockDim.x;
     const int64_t base = (int64_t)blockIdx.x * chunk;
     const int64_t end = base + chunk < b.n ? base + chunk : b.n;
+    if constexpr (DIRECT) {
+        const int64_t p = base + tid;
+        bool eq = p < end && (tid & 63) != 0;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const int c = p < end ? b.cell[d][p] : -1;
+            eq = eq & (c == __shfl_up(c, 1, 64));
+        }
+        int *const scratch = reinterpret_cast<int *>(smem_raw);
+        const int in_wave = __popcll(__ballot(eq));
+        if ((tid & 63) == 0)
+            scratch[tid >> 6] = in_wave;
+        __syncthreads();
+        int same = 0;
+        for (int w = 0; w < nth >> 6; ++w)
+            same += scratch[w];
+        __syncthreads();   // the scratch is free again
+        if (2 * same <= nth) {   // uniform
+            int c0[3], kap[3];
+            T f0[3], f1[3];
+            if (p < end && load_move(b, a, p, pc.n, c0, f0, f1, kap, err))
+                deposit_global_full<T, O>(pc, fp, c0, f0, f1, kap, b.w ? b.w[p] : pc.w0);
+            return;
+        }
+    }
     int len = chunk;
     for (int64_t s0 = base; s0 < end;) {
         const int seg = (int)(end - s0 < len ? end - s0 : len);
         const CellBox bx = segment_box(b, pc.n, s0, seg, reinterpret_cast<int *>(smem_raw));
         int ext[3];
-        const bool fits = bx.any && box_region(bx, halo, (size_t)room, ext);
+        size_t vol_box;
+        const bool fits = bx.any && box_region(bx, halo, (size_t)room, ext, vol_box);
         if (bx.any && !fits && len > OPS_MIN) {
             len >>= 1;   // uniform
             continue;
@@ -2887,14 +2972,50 @@ hipError_t launch_particles_global(int order, const PConst<T> &pc, const PArr<T>
 }
 
 // consecutive particles per workgroup of the box kernels: a tile's worth at
-// 8 per cell, less on a small species so that there are two workgroups per
-// CU (not below OPS_MIN)
+// 8 per cell, less on a small species so that there are two workgroups per CU.
+// Below 512 the boxes' halos cost more, so these are for species that would
+// leave a quarter of the CUs without a workgroup (order 3, binned, runs of 128
+// / 256 / 512: 32 K particles, FP32 gather 69 / 69 / 73 us, deposit drifted
+// from its tiles 96 / 93 / 191 us; 110 K, deposit 144 / 107 / 91 us).
 static int ops_chunk(int64_t n)
 {
     int c = 4096;
     while (c > OPS_MIN && n < (int64_t)c * 512)
         c >>= 1;
+    while (c > 128 && n < (int64_t)c * 192)
+        c >>= 1;
     return c;
+}
+
+// launch of a box kernel: particles and threads per workgroup, LDS bytes
+struct OpsPlan {
+    int chunk, threads;
+    size_t lds;
+};
+
+static OpsPlan ops_plan(int chunk, int threads, size_t lds)
+{
+    return OpsPlan{chunk, chunk < threads ? chunk : threads, lds};
+}
+
+// The gather's runs: a CU takes as many as its share rounded up, and a shorter
+// run costs more per particle (its halo, GATHER_HALO particles' worth here) but
+// leaves less of the last round empty (2.2 M particles, 2 per cell, FP32: 2.15
+// runs of 4096 per CU 142 us, 8.6 of 1024 125 us).
+constexpr int GATHER_HALO = 192, GATHER_CUS = 256;
+
+static int gather_chunk(int64_t n)
+{
+    int best = ops_chunk(n);
+    int64_t least = INT64_MAX;
+    for (int c = best; c >= OPS_MIN; c >>= 1) {
+        const int64_t per = (int64_t)c * GATHER_CUS, t = (n + per - 1) / per * (c + GATHER_HALO);
+        if (t < least) {
+            least = t;
+            best = c;
+        }
+    }
+    return best;
 }
 
 template <typename T, int O>
@@ -2903,11 +3024,24 @@ static hipError_t launch_gather_o(const PConst<T> &pc, const PArr<T> &sp, const 
 {
     static bool attr = false;
     allow_big_lds(&k_gather_box<T, O>, attr);
-    const int chunk = ops_chunk(sp.n);
-    const size_t lds = OpsThreads<T>::gather_lds;
-    const int room = (int)((lds - OPS_HEAD) / (6 * sizeof(T)));
-    hipLaunchKernelGGL((k_gather_box<T, O>), dim3(nblk(sp.n, chunk)), dim3(OpsThreads<T>::gather), lds, st, pc, sp, f,
-                       Ep[0], Ep[1], Ep[2], Bp[0], Bp[1], Bp[2], chunk, room, err);
+    if constexpr (O == 1) {
+        // The window's 48 reads per particle come from the caches as fast as
+        // a box can be staged, unless many particles share it.  A call, one
+        // particle per thread / boxes: FP32, binned, 8 per cell, 32 K 63.6 /
+        // 66.8 us, 262 K 74 / 71 us, 2 M 148 / 92 us; 2 per cell, 1 M 103 /
+        // 93 us; FP64, 8 per cell, 512 K 86 / 107 us, 1.4 M 112 / 117 us, 2 M
+        // 131 / 114 us; 2 per cell, 2.2 M, in no order 951 / 1187 us.
+        const bool dense = sp.n >= 4 * (int64_t)pc.n[0] * pc.n[1] * pc.n[2];
+        if (sizeof(T) == 4 ? sp.n < ((int64_t)1 << 17) : sp.n < ((int64_t)3 << 19) || !dense) {
+            hipLaunchKernelGGL((k_gather<T, O>), dim3(nblk(sp.n, 256)), dim3(256), 0, st, pc, sp, f, Ep[0], Ep[1],
+                               Ep[2], Bp[0], Bp[1], Bp[2], err);
+            return hipGetLastError();
+        }
+    }
+    const OpsPlan P = ops_plan(gather_chunk(sp.n), OpsThreads<T>::gather, OpsThreads<T>::gather_lds);
+    const int room = (int)((P.lds - OPS_HEAD) / (6 * sizeof(T)));
+    hipLaunchKernelGGL((k_gather_box<T, O>), dim3(nblk(sp.n, P.chunk)), dim3(P.threads), P.lds, st, pc, sp, f, Ep[0],
+                       Ep[1], Ep[2], Bp[0], Bp[1], Bp[2], P.chunk, room, err);
     return hipGetLastError();
 }
 
@@ -2936,13 +3070,28 @@ template <typename T, int O>
 static hipError_t launch_deposit_o(const PConst<T> &pc, const PArr<T> &before, const PArr<T> &after,
                                    const FieldPtrs<T> &f, int *err, hipStream_t st)
 {
-    static bool attr = false;
-    allow_big_lds(&k_deposit_box<T, O>, attr);
-    const int chunk = ops_chunk(before.n);
-    const size_t lds = 160 * 1024;
-    const int room = (int)((lds - OPS_HEAD - 2 * (size_t)chunk) / (3 * sizeof(double)));
-    hipLaunchKernelGGL((k_deposit_box<T, O>), dim3(nblk(before.n, chunk)), dim3(OpsThreads<T>::deposit), lds, st, pc,
-                       before, after, f, chunk, room, err);
+    // At first order 40 KB hold the box of a run of 256, which leaves four
+    // workgroups per CU; from 2^19 on a tile's worth per run saves more of the
+    // boxes' halos (binned, 8 per cell, 512 K 101 / 120 us, 884 K 127 / 122 us;
+    // 2 per cell, 524 K 102 / 95 us).  Below 49152 see k_deposit_box (64 K, 2
+    // per cell, drifted from its tiles: 75 us with boxes, 89 without).
+    const OpsPlan P = O == 1 && before.n < ((int64_t)1 << 19)
+                          ? ops_plan(256, 256, 40 * 1024)
+                          : ops_plan(ops_chunk(before.n), OpsThreads<T>::deposit, 160 * 1024);
+    const int room = (int)((P.lds - OPS_HEAD - 2 * (size_t)P.chunk) / (3 * sizeof(double)));
+    auto launch = [&](auto *kernel, bool &attr) {
+        allow_big_lds(kernel, attr);
+        hipLaunchKernelGGL(kernel, dim3(nblk(before.n, P.chunk)), dim3(P.threads), P.lds, st, pc, before, after, f,
+                           P.chunk, room, err);
+    };
+    static bool attr = false, attr_direct = false;
+    if constexpr (O == 1) {
+        if (before.n < 49152) {
+            launch(&k_deposit_box<T, O, true>, attr_direct);
+            return hipGetLastError();
+        }
+    }
+    launch(&k_deposit_box<T, O, false>, attr);
     return hipGetLastError();
 }
 

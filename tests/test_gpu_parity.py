@@ -236,6 +236,52 @@ def test_separate_gather_and_deposit_on_boxes_match_oracle(order, dtype, layout)
     assert rel_l2(_cpu(df.J), of.J) < (F64_TOL if dtype == "f64" else 1e-5)
 
 
+@pytest.mark.parametrize("order, dtype, n, grid, layout", [
+    (1, "f32", 60001, (32, 24, 40), "tiles"),        # deposit on boxes of runs of 256, gather per particle
+    (1, "f64", 60001, (32, 24, 40), "scattered"),    # ... whose boxes do not fit
+    (1, "f32", 140003, (32, 24, 40), "tiles"),       # gather on boxes too
+    (1, "f64", 1600003, (64, 48, 40), "cells"),      # ... in FP64, runs of 2048
+    (3, "f32", 40009, (32, 24, 40), "scattered"),    # runs of 128
+    (3, "f64", 90001, (32, 24, 40), "tiles"),        # runs of 256
+    (3, "f32", 600011, (240, 40, 32), "cells"),      # rows wider than a box: halved to 256
+    (3, "f64", 600011, (240, 40, 32), "cells"),      # ... or the rest of the run per particle
+])
+def test_separate_gather_and_deposit_over_species_sizes_match_oracle(order, dtype, n, grid, layout):
+    """The runs, threads and forms that the separate gather and deposit take
+    over the size of the species, with a partial last run; the bounds of the
+    test above."""
+    g = wl.plasma_grid(grid, order)
+    ncell = grid[0] * grid[1] * grid[2]
+    k = torch.arange(n)
+    if layout == "scattered":
+        cell = torch.randint(0, ncell, (n,), generator=torch.Generator().manual_seed(75))
+        cells = torch.stack([cell % grid[0], cell // grid[0] % grid[1], cell // (grid[0] * grid[1])])
+    elif layout == "cells":
+        cell = k * ncell // n
+        cells = torch.stack([cell % grid[0], cell // grid[0] % grid[1], cell // (grid[0] * grid[1])])
+    else:   # 8^3 tiles, every cell of a tile in turn
+        per = -(-n // (ncell // 512))
+        tile, cell = k // per, k % 512
+        cells = torch.stack([tile % (grid[0] // 8) * 8 + cell % 8,
+                             tile // (grid[0] // 8) % (grid[1] // 8) * 8 + cell // 8 % 8,
+                             tile // (grid[0] * grid[1] // 64) * 8 + cell // 64])
+    before = random_species(g, n, 76, dtype=dtype, cells=cells.to(torch.int32).contiguous())
+    after = _displaced(g, before, 77, amp=0.05)
+    f = random_fields(g, 78, dtype=dtype)
+    Ep, Bp = _lib.pic_gather(g, dev(before), dev(f))
+    df = dev(f)
+    df.J.fill_(0.25)
+    _lib.pic_deposit(g, dev(before), dev(after), df)
+    torch.cuda.synchronize()
+    oE, oB = oracle.gather(g, before.numpy(), f.numpy())
+    of = f.numpy()
+    of.J[:] = 0.25
+    oracle.deposit(g, before.numpy(), after.numpy(), of)
+    assert max_rel(_cpu(Ep), oE) < (F64_TOL if dtype == "f64" else 2e-6)
+    assert max_rel(_cpu(Bp), oB) < (F64_TOL if dtype == "f64" else 2e-6)
+    assert rel_l2(_cpu(df.J), of.J) < (F64_TOL if dtype == "f64" else 1e-5)
+
+
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 def test_yee_matches_oracle_with_source(dtype):
     g = _grid((16, 12, 20))
