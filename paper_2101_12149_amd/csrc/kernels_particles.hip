@@ -3160,29 +3160,35 @@ size_t adjoint_push_lds(const TileGeo &tg)
 
 // The same with rows padded so that eight cells of neighbouring rows fall on
 // different banks (as the forward tile kernel's), as far as the LDS has room
-// beside `more` bytes: the fields' rows, then hatE's too.  Returns the bytes
-// taken, 0 if not even the unpadded regions fit.  (With the staging of several
-// rows at a time, a laser box of 2 per cell 6.9 -> 6.2 ms for the pass; at 8
+// beside `more` bytes and a CU still holds as many workgroups: the fields'
+// rows, then hatE's too.  Returns the bytes taken, 0 if not even the unpadded
+// regions fit.  (Laser box, 2 per cell, particle passes 11.62 ms with the
+// padding, 11.65 without; but 119 x 120 x 180 in 7 x 6 x 6 tiles, 2 per cell,
+// first order, 1.23 ms where it left one workgroup per CU, 1.00 with two.  At 8
 // per cell the gradients leave no room, and fewer threads to make some cost
 // more: 128^3, the whole reverse step, 3.58 ms at 768, 3.71 at 704 with it.)
 template <typename T>
 static size_t adjoint_push_layout(TileGeo &tg, size_t more)
 {
+    const size_t limit = 160 * 1024, bare = adjoint_push_lds<T>(tg) + more;
+    if (bare > limit)
+        return 0;
     const int banks = 128 / (int)sizeof(T), t0 = tg.t[0] % banks;
     auto pitch = [&](int p, bool pad) {
         while (pad && p % banks != t0 && p % banks != banks - t0)
             ++p;
         return p;
     };
+    size_t l = 0;
     for (int pad = 2; pad >= 0; --pad) {
         tg.pr = pitch(6 * tg.rf[0], pad > 0);
         tg.ps = tg.pr * tg.rf[1];
         tg.jq = pitch(3 * tg.rj[0], pad > 1);
-        const size_t l = ((size_t)tg.ps * tg.rf[2] + (size_t)tg.jq * tg.rj[1] * tg.rj[2]) * sizeof(T) + 16 + more;
-        if (l <= 160 * 1024)
-            return l;
+        l = ((size_t)tg.ps * tg.rf[2] + (size_t)tg.jq * tg.rj[1] * tg.rj[2]) * sizeof(T) + 16 + more;
+        if (l <= limit && limit / l == limit / bare)
+            break;
     }
-    return 0;
+    return l;
 }
 
 // dynamic LDS one workgroup of the tiled adjoint scatter may take

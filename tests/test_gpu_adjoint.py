@@ -263,6 +263,17 @@ def test_tiled_adjoint_over_tile_shapes_matches_oracle(tile, ppc, order, dtype):
         assert rel_l2(_cpu(getattr(dlam, name)), getattr(olam, name)) < tol, name
 
 
+@pytest.mark.parametrize("tile, ppc, order, dtype", [
+    ((7, 6, 6), 2, 1, "f32"),    # padded rows would leave one workgroup per CU
+    ((4, 5, 4), 3, 3, "f32"),    # ... hatE's would
+    ((4, 4, 4), 2, 1, "f32"),    # several workgroups per CU, padded
+    ((4, 4, 4), 2, 1, "f64"),
+])
+def test_tiled_adjoint_layouts_by_workgroups_per_cu_match_oracle(tile, ppc, order, dtype):
+    """The reverse step's LDS layouts where several workgroups share a CU."""
+    test_tiled_adjoint_over_tile_shapes_matches_oracle(tile, ppc, order, dtype)
+
+
 @pytest.mark.parametrize("tiled", [False, True])
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 def test_adjoint_on_the_smallest_grid_with_every_option(dtype, tiled):
