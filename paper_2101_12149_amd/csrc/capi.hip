@@ -225,38 +225,52 @@ void region_extents(int order, TileGeo &tg)
 }
 
 // LDS layout of the one-pass tile kernel.  Lanes are consecutive cells along
-// x, then y, then z: with pitches that equal the tile's modulo 32 words (rows
-// of six interleaved field components, planes), consecutive lanes fall on
-// consecutive banks.  The rows of a current component are too short for that
-// on wide tiles; folded rows of 16 values do the same there.  What is left
-// over holds the queue of cell-crossing particles, up to 1024: two ints each,
-// and their offsets too where there is room (first order, and tiles of at
-// most 64 cells, which take 256).  Where the padded regions leave room for
-// less than 256, the rows stay unpadded.
+// x, then y, then z: with pitches that equal the tile's (or its negative)
+// modulo 32 words (rows of six interleaved field components, planes),
+// consecutive lanes fall on consecutive banks.  The rows of a current component
+// are too short for that on tiles of seven or eight cells; folded rows of 16
+// values do the same there (on narrower ones three rows share the banks and
+// folding only takes LDS).  What is left over holds the queue of cell-crossing
+// particles, up to 1024: two ints each, and their offsets too where that leaves
+// room for 256.  The layout with the most padding whose queue takes 256 is
+// chosen, else the bare regions (third order: by component).  FP64 order 3, particle kernel
+// with and without each: 128^3, 8 per cell (8 x 8 x 4 tiles) folded 12.5, rows
+// padded 13.3, bare 15.0 ms; 75 x 108 x 72, 6 per cell (5 x 6 x 8) folded, for
+// which nothing else is padded, 8.5, rows padded 7.3 ms; 108 x 110 x 57, 4 per
+// cell, hot (6 x 5 x 3) offsets in memory 3.10, in the queue 2.98 ms; 210 x 224
+// x 225, 1 per cell (7 x 8 x 5) bare interleaved rows 26.5, by component 25.6 ms.
 void tile_layout(GridInfo &gi, size_t limit)
 {
     TileGeo &tg = gi.tg;
     const int banks = 128 / (int)gi.tsize;   // values
-    for (int pad = 1; pad >= 0; --pad) {
-        tg.pr = 6 * tg.rf[0];
-        tg.jq = tg.rj[0];
-        tg.fold = 0;
-        if (pad) {
-            tg.pr += (tg.t[0] + banks - tg.pr % banks) % banks;
-            if (gi.order == 3 && tg.t[0] > 4 && tg.rj[0] <= 16 && tg.rj[1] % 2 == 1) {
-                tg.jq = 16;
-                tg.fold = 8;
-            }
+    auto pitch = [&](int p, int t) {
+        t %= banks;
+        while (p % banks != t && p % banks != (banks - t) % banks)
+            ++p;
+        return p;
+    };
+    const bool folds = gi.order == 3 && (tg.t[0] == 7 || tg.t[0] == 8) && tg.rj[0] <= 16 && tg.rj[1] % 2 == 1;
+    const bool small = tg.t[0] * tg.t[1] * tg.t[2] <= 64;
+    const size_t most = small ? 256 : 1024;
+    for (int pad = folds ? 2 : 1; pad >= 0; --pad) {
+        tg.fold = pad == 2;
+        tg.jq = tg.fold ? 16 : tg.rj[0];
+        if (pad > 0 || gi.order == 1) {
+            tg.pm = tg.rf[0];
+            tg.pr = pad > 0 ? pitch(6 * tg.rf[0], tg.t[0]) : 6 * tg.rf[0];
+            tg.ps = pad > 0 ? pitch(tg.pr * tg.rf[1], tg.t[0] * tg.t[1]) : tg.pr * tg.rf[1];
+            tg.fvol = tg.ps * tg.rf[2];
+        } else {
+            tg.pr = tg.rf[0];
+            tg.ps = tg.pr * tg.rf[1];
+            tg.pm = tg.ps * tg.rf[2];
+            tg.fvol = 6 * tg.pm;
         }
-        tg.ps = tg.pr * tg.rf[1];
-        if (pad)
-            tg.ps += (tg.t[0] * tg.t[1] + banks - tg.ps % banks) % banks;
-        const size_t used = (((size_t)tg.ps * tg.rf[2] * gi.tsize + 15) & ~size_t(15)) +
+        const size_t used = (((size_t)tg.fvol * gi.tsize + 15) & ~size_t(15)) +
                             tile_current_values(tg) * sizeof(double) + sizeof(int);
-        const bool small = tg.t[0] * tg.t[1] * tg.t[2] <= 64;
-        tg.qoff = small || gi.order == 1;
-        const size_t entry = 2 * sizeof(int) + (tg.qoff ? 6 * gi.tsize : 0), most = small ? 256 : 1024;
-        const size_t room = limit > used ? (limit - used) / entry : 0;
+        const size_t left = limit > used ? limit - used : 0, full = 2 * sizeof(int) + 6 * gi.tsize;
+        tg.qoff = small || gi.order == 1 || pad == 0 || left / full >= 256;
+        const size_t room = left / (tg.qoff ? full : 2 * sizeof(int));
         tg.qcap = (int)(room < most ? room : most);
         if (tg.qcap >= 256)
             break;

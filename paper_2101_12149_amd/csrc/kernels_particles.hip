@@ -467,14 +467,16 @@ __device__ __attribute__((always_inline)) inline void deposit_still_shared(const
 // wave's 384 field reads and some 200 atomics kept it 82 % busy, half of that
 // time on bank conflicts, against 37 % for the vector unit.  With the padded
 // and folded rows of tile_layout (which take 43 % of the conflict cycles away)
-// and 12 waves, 128^3 / 8 per cell went from 3.74 to 3.18 ms a step, 64^3 / 4
-// per cell from 282 to 250 us.  Staggered windows along y at five
+// and 12 waves, 128^3 / 8 per cell went from 3.74 to 3.12 ms a step, 64^3 / 4
+// per cell from 288 to 249 us.  Staggered windows along y at five
 // fixed rows, which never conflict, read more than they saved (3.22 ms).
+// FOLD: the current rows are folded (a constant, as the index arithmetic costs
+// 1-2 % where they are not).
 //
 // The particles left to k_particles_strays are listed (`strays`) before they
 // move: when the step runs in place their cells are overwritten, so the
 // stray kernel could not tell them from the cells any more.
-template <typename T, int O, bool G, int NTH>
+template <typename T, int O, bool G, int NTH, bool FOLD>
 __global__ void __launch_bounds__(NTH) k_particles_tile(PConst<T> pc, TileGeo tg, PArr<T> in, PArr<T> out,
                                                         FieldPtrs<T> fp, const int *__restrict__ tile_start,
                                                         StrayList strays, GuestArgs g, Off3<T> f0s, int *err)
@@ -484,9 +486,9 @@ __global__ void __launch_bounds__(NTH) k_particles_tile(PConst<T> pc, TileGeo tg
     const int rjx = tg.rj[0], rjy = tg.rj[1];
     const int rjvol = tg.jq * rjy * tg.rj[2], rjall = tile_current_values(tg);
     // the current tile accumulates in FP64 (fast LDS atomics), after the fields
-    double *sJ = reinterpret_cast<double *>(smem_raw + ((tg.ps * tg.rf[2] * sizeof(T) + 15) & ~size_t(15)));
-    // (first-order tiles are not folded, and their queue holds the offsets)
-    const int fold = O == 3 ? tg.fold : 0;
+    double *sJ = reinterpret_cast<double *>(smem_raw + ((tg.fvol * sizeof(T) + 15) & ~size_t(15)));
+    constexpr int fold = FOLD ? LDS_FOLD : 0;
+    // (the queue of a first-order tile always holds the offsets)
     const bool qoff = O == 1 || tg.qoff;
     // then the queue of cell-crossing particles: offsets, indices, moves, count
     CrossQueue<T> cq;
@@ -503,7 +505,11 @@ __global__ void __launch_bounds__(NTH) k_particles_tile(PConst<T> pc, TileGeo tg
         return;   // uniform across the workgroup
 
     const int tid = threadIdx.x, nth = blockDim.x;
-    stage_fields<O == 1 ? 1 : sizeof(T) == 4 ? 4 : 2>(fp, pc.n, tg, ts.t0, sF, tg.rf[0], tg.pr, tg.ps);
+    // (first-order rows are interleaved in any layout)
+    const int pm = O == 1 ? tg.rf[0] : tg.pm;
+    // (in FP64 two rows at a time cost 1-3 %: 162 x 248 x 222, 1 per cell 4.24 /
+    // 4.10 ms a step)
+    stage_fields<O == 3 && sizeof(T) == 4 ? 4 : 1>(fp, pc.n, tg, ts.t0, sF, pm, tg.pr, tg.ps);
     for (int r = tid; r < rjall; r += nth)
         sJ[r] = 0.0;
     if (tid == 0)
@@ -513,7 +519,7 @@ __global__ void __launch_bounds__(NTH) k_particles_tile(PConst<T> pc, TileGeo tg
     FieldSrc<T> lf;
 #pragma unroll
     for (int m = 0; m < 6; ++m)
-        lf.c[m] = sF + m * tg.rf[0];
+        lf.c[m] = sF + m * pm;
     const int sf[3] = {1, tg.pr, tg.ps};
     const int sj[3] = {1, tg.jq, tg.jq * rjy};
     const int np = (int)(ts.pe - ts.ps);
@@ -2828,7 +2834,7 @@ static inline unsigned nblk(int64_t n, int b)
 template <typename T>
 size_t tile_lds_bytes(int, const TileGeo &tg)
 {
-    return (((size_t)tg.ps * tg.rf[2] * sizeof(T) + 15) & ~size_t(15)) + tile_current_values(tg) * sizeof(double) +
+    return (((size_t)tg.fvol * sizeof(T) + 15) & ~size_t(15)) + tile_current_values(tg) * sizeof(double) +
            (size_t)tg.qcap * (2 * sizeof(int) + (tg.qoff ? 6 * sizeof(T) : 0)) + sizeof(int);
 }
 
@@ -2860,12 +2866,49 @@ int cells_chunk(const TileGeo &tg, TileGeo &tq)
     return (int)(kc < 16384 ? kc : 16384);
 }
 
+// launch of the one-pass tile kernel
+template <typename T>
+struct OnePass {
+    const PConst<T> &pc;
+    const TileGeo &tg;
+    const PArr<T> &in, &out;
+    const FieldPtrs<T> &f;
+    const int *tile_start;
+    const StrayList &stray;
+    const GuestArgs &g;
+    const Off3<T> &f0s;
+    int *err;
+    size_t lds;
+    hipStream_t st;
+};
+
+template <typename T, int O, bool G, int NTH, bool FOLD>
+static hipError_t launch_one_pass(const OnePass<T> &a)
+{
+    static bool attr = false;
+    allow_big_lds(&k_particles_tile<T, O, G, NTH, FOLD>, attr);
+    const unsigned ntiles = (unsigned)(a.tg.nt[0] * a.tg.nt[1] * a.tg.nt[2]);
+    hipLaunchKernelGGL((k_particles_tile<T, O, G, NTH, FOLD>), dim3(ntiles), dim3(NTH), a.lds, a.st, a.pc, a.tg, a.in,
+                       a.out, a.f, a.tile_start, a.stray, a.g, a.f0s, a.err);
+    return hipGetLastError();
+}
+
+template <typename T, int O, int NTH>
+static hipError_t launch_one_pass_guests(const OnePass<T> &a)
+{
+    if constexpr (O == 3) {
+        if (a.tg.fold)
+            return a.g.flag_next ? launch_one_pass<T, O, true, NTH, true>(a)
+                                 : launch_one_pass<T, O, false, NTH, true>(a);
+    }
+    return a.g.flag_next ? launch_one_pass<T, O, true, NTH, false>(a) : launch_one_pass<T, O, false, NTH, false>(a);
+}
+
 template <typename T, int O>
 static hipError_t launch_tile_o(const PConst<T> &pc, const TileGeo &tg, const PArr<T> &in, const PArr<T> &out,
                                 const FieldPtrs<T> &f, const int *tile_start, const StrayList &stray,
                                 const GuestArgs &g, T *const scratch[3], int *err, hipStream_t st)
 {
-    static bool attr_plain = false, attr_guests = false, attr_few = false, attr_few_guests = false;
     static bool attr_cp = false, attr_cg = false;
     const unsigned ntiles = (unsigned)(tg.nt[0] * tg.nt[1] * tg.nt[2]);
     // FP32 order 3 runs on the matrix cores (256^3, 8 per cell: 15.1 -> 12.8
@@ -2905,27 +2948,16 @@ static hipError_t launch_tile_o(const PConst<T> &pc, const TileGeo &tg, const PA
         (void)attr_cg;
     }
     const size_t lds = tile_lds_bytes<T>(O, tg);
-    auto launch = [&](auto *kernel, bool &attr, int nth) {
-        allow_big_lds(kernel, attr);
-        hipLaunchKernelGGL(kernel, dim3(ntiles), dim3(nth), lds, st, pc, tg, in, out, f, tile_start, stray, g, f0s,
-                           err);
-    };
-    constexpr int most = TileThreads<T, O>::value;
+    const OnePass<T> a{pc, tg, in, out, f, tile_start, stray, g, f0s, err, lds, st};
     // Every wave stages and flushes, but tiles of few particles end sooner
     // with fewer waves of more registers: FP64 at 512 / 768 threads, 128^3, 8
     // per cell (2048 per tile) 3.25 / 3.19 ms a step; 16^3, 2 per cell (128)
     // 15.6 / 16.8 us.
-    if (most > 512 && sizeof(T) == 8 && in.n <= (int64_t)512 * ntiles) {
-        if (g.flag_next)
-            launch(&k_particles_tile<T, O, true, 512>, attr_few_guests, 512);
-        else
-            launch(&k_particles_tile<T, O, false, 512>, attr_few, 512);
-    } else if (g.flag_next) {
-        launch(&k_particles_tile<T, O, true, most>, attr_guests, most);
-    } else {
-        launch(&k_particles_tile<T, O, false, most>, attr_plain, most);
+    if constexpr (sizeof(T) == 8 && O == 3) {
+        if (in.n <= (int64_t)512 * ntiles)
+            return launch_one_pass_guests<T, O, 512>(a);
     }
-    return hipGetLastError();
+    return launch_one_pass_guests<T, O, TileThreads<T, O>::value>(a);
 }
 
 template <typename T>

@@ -313,8 +313,10 @@ __device__ __attribute__((always_inline)) inline void stage_fields(const FieldPt
 
 // An index into rows of 16 values, the halves of every second row exchanged:
 // sixteen lanes that add to eight cells of two neighbouring rows then fall on
-// all the LDS banks, as they would not at any pitch below 24.  fold is 8, or
-// 0 for rows of another pitch.
+// all the LDS banks, as they would not at any pitch below 24.  fold is LDS_FOLD,
+// or 0 for rows of another pitch.
+constexpr int LDS_FOLD = 8;
+
 __device__ inline int lds_fold(int i, int fold)
 {
     return i ^ ((i >> 1) & fold);

@@ -47,9 +47,10 @@ struct TileGeo {
     int lo_f, rf[3];
     int lo_j, rj[3];
     int jp;        // row pitch of an unpadded current tile in LDS (rj[0])
-    // the one-pass tile kernel's: pitch of a row of six field components and
-    // of a plane, pitch of a row of a current component, and its lds_fold
-    int pr, ps, jq, fold;
+    // the one-pass tile kernel's: pitches of a field component, a row and a
+    // plane, the values of all six; pitch of a row of a current component, and
+    // whether these are folded (lds_fold)
+    int pm, pr, ps, fvol, jq, fold;
     int xcd_map;   // spread consecutive tiles so each XCD gets a contiguous block
     int qcap;      // entries of the tile kernel's LDS queue of cell-crossing particles
     int qoff;      // the queue holds their offsets too

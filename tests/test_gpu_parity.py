@@ -882,6 +882,20 @@ def test_one_pass_tile_kernel_layouts_match_oracle(dtype, ppc, order, tile, slac
         assert max_rel(_cpu(gsp.u), osp.u) < F64_TOL
 
 
+@pytest.mark.parametrize("tile, slack, order", [
+    ((8, 6, 6), 1, 3),    # folding does not fit: rows padded, the crossers' offsets in memory
+    ((6, 8, 6), 1, 3),    # rows padded to the negative pitch
+    ((6, 5, 3), 1, 3),    # the queue holds the offsets beside padded rows
+    ((7, 7, 6), 1, 3),    # bare regions by component
+    ((12, 12, 8), 0, 1),  # bare first-order rows
+])
+@pytest.mark.parametrize("ppc", [1, 6])
+def test_one_pass_tile_kernel_layouts_of_wide_tiles_match_oracle(ppc, tile, slack, order):
+    """More of the one-pass tile kernel's LDS layouts in FP64, below and above
+    the 512 particles per tile that its threads go by."""
+    test_one_pass_tile_kernel_layouts_match_oracle("f64", ppc, order, tile, slack)
+
+
 def test_guest_lists_overflow_to_the_stray_path():
     """64 ppc at u_th = 0.9c on 16^3, sorted once and then stepped without
     re-sorting: thousands of particles per tile leave their home region each
