@@ -826,6 +826,54 @@ def test_f32_order3_tile_step_leaves_corrupt_particles_out(npart):
     assert max_rel(_cpu(sp.u)[:, keep.numpy()], o.u) < 4e-6
 
 
+@pytest.mark.parametrize("case", [
+    # tiles of more than 640 cells, which the matrix-core kernels leave to the others; columns as above
+    ((24, 16, 16), (12, 8, 8), 0, 12288, 0, True, False, 3),    # 2 per cell: the one-pass kernel
+    ((16, 20, 18), (8, 10, 9), 0, 11520, 0, False, True, 3),    # ... with folded current rows
+    ((32, 16, 16), (16, 8, 8), 0, 16384, 0, True, False, 3),
+    ((24, 16, 16), (12, 8, 8), 0, 43008, 0, False, True, 3),    # 7 per cell: the two-phase kernel, with guests
+    ((16, 20, 18), (8, 10, 9), 0, 46080, 0, True, False, 3),
+])
+def test_f32_order3_tile_step_on_large_tiles_matches_oracle(case):
+    """The kernels that FP32 third order falls back to on large tiles, with
+    stale binnings and, from the second step on, guests."""
+    test_f32_order3_tile_step_matches_oracle(case)
+
+
+@pytest.mark.parametrize("npart", [8200, 28000])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_f32_order3_value_beyond_a_particles_window_is_not_read(axis, npart):
+    """The matrix-core kernels read five nodes along a staggered axis, of which
+    a particle's window has four: an infinite field value at the fifth leaves
+    the particle as it would be with any other value there (momenta within the
+    gather's and push's 4e-6, J within rel-L2 1e-5 of the oracle's, which has a
+    finite value)."""
+    g = wl.plasma_grid((16, 16, 16), 3)
+    g.tile, g.slack = (8, 8, 8), 1
+    rng = np.random.default_rng(143)
+    cells = np.stack([rng.integers(0, 16, npart), rng.integers(0, 16, npart), rng.integers(0, 5, npart)])
+    probe = np.array([10, 4, 10])
+    cells[:, :3] = probe[:, None]
+    sp = random_species(g, npart, 144, u_th=0.1, dtype="f32", cells=torch.tensor(cells.astype(np.int32)))
+    sp.off[:, :3] = torch.tensor([[0.1, 0.2, 0.4]] * 3)
+    f = random_fields(g, 145, scale=0.05, dtype="f32")
+    node = probe.copy()
+    node[axis] += 2        # below the middle of the cell the window ends at + 1
+    gsp, gf = dev(sp), dev(f)
+    gf.E[axis, node[2], node[1], node[0]] = float("inf")
+    ts = torch.zeros(_lib.pic_tile_count(g, "f32") + 1, dtype=torch.int32, device="cuda")
+    ws = _lib.workspace(g, "f32", npart)
+    perm = torch.empty(npart, dtype=torch.int32, device="cuda")
+    _lib.pic_sort_tiles(g, gsp, ts, ws, perm=perm)
+    _lib.pic_step(g, gsp, gf, None, 0, 1, 0, ts, ws, None)
+    torch.cuda.synchronize()
+    osp, of = sp.numpy(), f.numpy()
+    oracle.step(g, osp, of, None, 0, 1)
+    back = torch.argsort(perm.cpu().long())
+    assert max_rel(_cpu(gsp.u)[:, back.numpy()], osp.u) < 4e-6
+    assert rel_l2(_cpu(gf.J), of.J) < 1e-5
+
+
 @pytest.mark.parametrize("ppc", [2, 8])
 def test_f32_order3_particles_that_end_at_a_cell_face(ppc):
     """Every particle ends within a few roundings of a face of its cell, on
