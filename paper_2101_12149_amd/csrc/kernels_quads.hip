@@ -48,6 +48,7 @@ constexpr int QD_BATCH = 5;        // sparse tiles: batches of sixteen groups pe
 constexpr int QD_MIN_ROUND = 256;  // particles of a round, at least
 constexpr int QD_RESTAGE = 4096;   // cells that a tile of several rounds stages in all, at most
 constexpr int QD_CELLS = 640;      // cells of a tile, at most
+constexpr int QD_CUS = 256;        // compute units: so many tiles or fewer have one each
 constexpr int QD_STAGE = 4;        // rows of the field staging in flight together
 
 // Row pitches (in words) that spread a quad's columns over the LDS banks:
@@ -1116,14 +1117,17 @@ struct QuadPlan {
     int nth, round;
 };
 
-static QuadPlan quad_plan_as(const TileGeo &tg, int64_t want, int slots, bool share)
+static QuadPlan quad_plan_as(const TileGeo &tg, int64_t want, int64_t ntiles, int slots, bool share)
 {
     QuadPlan P{false, share, 0, 0};
     // the shared layout on half a CU's LDS: two workgroups
     const size_t limit = (share ? 80 : 160) * 1024;
     const int per = share ? 4 : 5, most = share ? 512 : 1024;
-    // tiles of few particles take fewer threads
-    P.nth = want <= 400 && slots <= 256 * QD_SLOTS ? 256 : (want <= 1600 || most == 512) ? 512 : 1024;
+    // tiles of few particles take fewer threads where several share a CU; a
+    // tile with a CU to itself ends sooner with all (16 x 20 x 35 in 80 tiles, 2
+    // per cell: 39.6 us a step with 256 threads, 33.6 with 512; 32^3 in 512
+    // tiles, 1 per cell: 32.9 / 35.8 us)
+    P.nth = want <= 400 && ntiles > QD_CUS && slots <= 256 * QD_SLOTS ? 256 : (want <= 1600 || most == 512) ? 512 : 1024;
     if (slots > P.nth * QD_SLOTS)
         P.nth = most;
     if (slots > P.nth * QD_SLOTS)
@@ -1139,7 +1143,9 @@ static QuadPlan quad_plan_as(const TileGeo &tg, int64_t want, int slots, bool sh
 }
 
 // The shared layout stages and flushes its regions once a round, so it takes
-// the tiles of one round, and of a few where the regions are small.  Shared
+// the tiles of one round, and of a few where the regions are small and the two
+// workgroups on a CU overlap (14 x 21 x 16 in 24 tiles, 12 per cell: 85.3 us a
+// step in two rounds, 63.0 dense).  Shared
 // against dense, particle kernel of four steps: 160^3, 8^3 tiles, 3 / 4 / 6
 // per cell (one round, then two) 5.5 / 9.2 / 10.3 against 6.8 / 7.8 / 9.9 ms;
 // 128^3, 8 x 8 x 4 tiles, 4 / 8 / 12 per cell 3.9 / 7.0 / 9.7 against
@@ -1160,12 +1166,19 @@ static QuadPlan quad_plan(const TileGeo &tg, int64_t n)
     if (cells > QD_CELLS)
         return QuadPlan{false, false, 0, 0};
     const int64_t ntiles = (int64_t)tg.nt[0] * tg.nt[1] * tg.nt[2];
+    // With a CU for each tile a step takes the latency of its longest tile, and
+    // groups of one particle need more batches than a workgroup has waves
+    // (42 x 20 x 35 in 120 tiles, 1 per cell: 32.6 us a step on one
+    // particle per thread, 37.6 in groups; 16^3 in 64 tiles 30.5 / 26.1 us).
+    if (ntiles <= QD_CUS && cells > 512 / 64 * 16 && 2 * n < 3 * cells * ntiles)
+        return QuadPlan{false, false, 0, 0};
     // what a tile holds on average, with room for uneven ones
     const int64_t want = (n + ntiles - 1) / ntiles * 9 / 8 + 64;
-    const QuadPlan S = quad_plan_as(tg, want, slots, true);
-    if (S.ok && (want <= S.round || (want + S.round - 1) / S.round * region <= QD_RESTAGE))
+    const QuadPlan S = quad_plan_as(tg, want, ntiles, slots, true);
+    if (S.ok && (want <= S.round ||
+                 (ntiles > QD_CUS && (want + S.round - 1) / S.round * region <= QD_RESTAGE)))
         return S;
-    return quad_plan_as(tg, want, slots, false);
+    return quad_plan_as(tg, want, ntiles, slots, false);
 }
 
 template <bool G, int PRC, int PSC, int RFX>

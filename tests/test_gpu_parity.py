@@ -840,6 +840,19 @@ def test_f32_order3_tile_step_on_large_tiles_matches_oracle(case):
     test_f32_order3_tile_step_matches_oracle(case)
 
 
+@pytest.mark.parametrize("case", [
+    # columns as above
+    ((16, 20, 35), (4, 5, 7), 1, 11000, 0, True, False, 3),     # few tiles, one particle per cell: one-pass kernel
+    ((16, 20, 35), (4, 5, 7), 1, 22000, 0, True, False, 3),     # two per cell: groups, all threads
+    ((28, 28, 28), (4, 4, 4), 1, 22000, 0, False, False, 3),    # more tiles than CUs: fewest threads
+    ((14, 21, 16), (7, 7, 4), 1, 56000, 0, True, False, 1),     # few tiles of more than a round: dense layout
+    ((28, 28, 28), (4, 4, 4), 1, 660000, 0, False, False, 1),   # many such: rounds of the shared layout
+])
+def test_f32_order3_tile_step_over_tile_counts_matches_oracle(case):
+    """What the FP32 third-order tile step chooses by the number of tiles."""
+    test_f32_order3_tile_step_matches_oracle(case)
+
+
 @pytest.mark.parametrize("npart", [8200, 28000])
 @pytest.mark.parametrize("axis", [0, 1, 2])
 def test_f32_order3_value_beyond_a_particles_window_is_not_read(axis, npart):
