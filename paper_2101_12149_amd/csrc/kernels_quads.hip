@@ -808,10 +808,19 @@ __device__ __attribute__((always_inline)) inline void quad_deposit_batch(const Q
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             acc[m][k] = f4{0.f, 0.f, 0.f, 0.f};
+    // Particles that no group of the wave holds are passed over (the first groups
+    // of all cells come first, so at low density whole waves hold one or two
+    // each): 96^3, 1 per cell, cold 245 -> 234 us a step, 256^3, 8 per cell 12.6
+    // -> 12.5 ms.
+    const int count = (int)((d >> 13) & 7);
     quad_deposit_particle<0>(poly, mv, m1, m2, acc);
-    quad_deposit_particle<1>(poly, mv, m1, m2, acc);
-    quad_deposit_particle<2>(poly, mv, m1, m2, acc);
-    quad_deposit_particle<3>(poly, mv, m1, m2, acc);
+    if (__ballot(count > 1)) {
+        quad_deposit_particle<1>(poly, mv, m1, m2, acc);
+        if (__ballot(count > 2)) {
+            quad_deposit_particle<2>(poly, mv, m1, m2, acc);
+            quad_deposit_particle<3>(poly, mv, m1, m2, acc);
+        }
+    }
     if (d != 0) {
         const int o[3] = {(int)((d >> 16) & 31) - sl + lo, (int)((d >> 21) & 31) - sl + lo, (int)(d >> 26) - sl + lo};
         double *a0[3];
