@@ -227,6 +227,8 @@ __global__ void __launch_bounds__(256) k_clear(ClearList c)
 
 hipError_t launch_clear(const ClearList &c, hipStream_t st)
 {
+    if (c.count > ClearList::MOST)
+        return hipErrorInvalidValue;
     int64_t most = 0;
     for (int i = 0; i < c.count; ++i)
         most = c.n[i] > most ? c.n[i] : most;

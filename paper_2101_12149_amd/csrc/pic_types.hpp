@@ -184,16 +184,21 @@ hipError_t launch_filter_z(const T *in, T *out, const T w[4], bool add, const in
 template <typename T>
 hipError_t launch_fill(T *p, int64_t n, T v, hipStream_t st);
 
-// arrays of n 4-byte words to clear
+// arrays of n 4-byte words to clear; launch_clear refuses a list to which more
+// than MOST were added
 struct ClearList {
+    static constexpr int MOST = 6;
     int count = 0;
-    int *p[6];
-    int64_t n[6];
+    int *p[MOST];
+    int64_t n[MOST];
     template <typename V>
     void add(V *q, int64_t values)
     {
-        p[count] = reinterpret_cast<int *>(q);
-        n[count++] = values * (int64_t)(sizeof(V) / sizeof(int));
+        if (count < MOST) {
+            p[count] = reinterpret_cast<int *>(q);
+            n[count] = values * (int64_t)(sizeof(V) / sizeof(int));
+        }
+        ++count;
     }
 };
 hipError_t launch_clear(const ClearList &c, hipStream_t st);
