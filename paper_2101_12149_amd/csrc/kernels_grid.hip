@@ -428,8 +428,11 @@ __global__ void __launch_bounds__(SEG_T) k_bin_count(PArr<T> sp, TileGeo tg, int
         return (tx + tg.nt[0] * (ty + tg.nt[1] * tz)) * tcells + (v[0] - tx * tg.t[0]) +
                tg.t[0] * ((v[1] - ty * tg.t[1]) + tg.t[1] * (v[2] - tz * tg.t[2]));
     };
-    // the particles are ranked in their order (a barrier between the chunks),
-    // so those that kept their cell keep their order in it
+    // The chunks are ranked in turn (a barrier between them), which keeps input
+    // that has an order near it.  It is not more than that: inside a chunk the
+    // waves' atomics come in any order, and so do the workgroups' ranges and
+    // the particles outside the region, so the order inside a cell is
+    // unspecified.
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
         kk[j] = cell_key(c[j]);
