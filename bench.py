@@ -124,21 +124,35 @@ def run_adjoint(w, nrep, tile_start):
     return dict(ms=e0.elapsed_time(e1), kernels=kt)
 
 
-def tile_kernel_name(npart, ncell, tsize, order):
-    """The fused particle kernel the library runs with its automatic tiles:
-    on the matrix cores for FP32 order 3, else the one-pass one."""
-    return "k_particles_quads" if tsize == 4 and order == 3 else "k_particles_tile"
+def tile_kernel_name(g, npart, dtype):
+    """The fused particle kernel the library runs: on the matrix cores for
+    FP32 order 3 (tiles of at most 640 cells; in 8^3-cell tiles the dense
+    layout where a round of half a CU's LDS, 1940 particles, does not hold an
+    average tile's with an eighth and 64 to spare), else the one-pass one, or
+    on larger FP32 order-3 tiles from 6 per cell on the two-phase one."""
+    from paper_2101_12149_amd import _lib
+    if dtype != "f32" or g.order != 3:
+        return "k_particles_tile"
+    tile, slack = _lib.pic_tile_shape(g, dtype)
+    if tile[0] * tile[1] * tile[2] > 640:
+        return "k_particles_cells" if npart >= 6 * g.ncells else "k_particles_tile"
+    if tuple(tile) != (8, 8, 8) or slack != 1:
+        return "k_particles_quads or k_particles_quads_dense"
+    per_tile = -(-npart // _lib.pic_tile_count(g, dtype))
+    return "k_particles_quads_dense" if per_tile * 9 // 8 + 64 > 1940 else "k_particles_quads"
 
 
-def kernel_roofs(kernels, npart, ncell, tsize, has_w, order):
+def kernel_roofs(kernels, w):
     """The fused tile kernel's mean launch time and its HBM and ALU
     fractions from the algorithmic bytes and flops per particle-step."""
+    npart, ncell, order = w.species.n, w.grid.ncells, w.grid.order
+    tsize = 4 if w.dtype == "f32" else 8
     ms, n = kernels["particles"]
     avg = ms / max(n, 1)
-    alg_bytes = particle_bytes(npart, tsize, has_w) + field_bytes(ncell, tsize)
+    alg_bytes = particle_bytes(npart, tsize, w.species.w is not None) + field_bytes(ncell, tsize)
     gbs = alg_bytes / (avg * 1e-3) / 1e9
     tfs = FLOPS_PER_PARTICLE[order] * npart / (avg * 1e-3) / 1e12
-    return {"kernel": tile_kernel_name(npart, ncell, tsize, order), "avg_ms": round(avg, 4),
+    return {"kernel": tile_kernel_name(w.grid, npart, w.dtype), "avg_ms": round(avg, 4),
             "alg_bytes_per_particle": round(alg_bytes / npart, 2),
             "hbm_GBps": round(gbs, 1), "hbm_frac": round(gbs / HBM_PEAK_GBS, 4), "alu_TFLOPs": round(tfs, 2),
             "alu_frac": round(tfs / VALU_PEAK_TFLOPS, 4)}
@@ -188,8 +202,7 @@ def bench_config(name, steps, warmup, nadj, window):
     from paper_2101_12149_amd import workloads as wl
     w = wl.named(name, device="cuda")
     g = w.grid
-    npart, ncell = w.species.n, g.ncells
-    tsize = 4 if w.dtype == "f32" else 8
+    npart = w.species.n
     init = (w.species.clone(), w.fields.clone()) if window else None
     fw = run_forward(w, steps, warmup, w.sort_every, name)
     ms = fw["ms"] / steps
@@ -197,7 +210,7 @@ def bench_config(name, steps, warmup, nadj, window):
            "steps": steps, "warmup": warmup, "ms_per_step": round(ms, 4),
            "particle_steps_per_s": npart * steps / (fw["ms"] * 1e-3),
            "kernels_ms_per_step": {k: round(v[0] / steps, 4) for k, v in fw["kernels"].items() if v[1]},
-           "dominant": kernel_roofs(fw["kernels"], npart, ncell, tsize, w.species.w is not None, g.order)}
+           "dominant": kernel_roofs(fw["kernels"], w)}
     adj = run_adjoint(w, nadj, fw["ts"])
     adj_ms = adj["ms"] / nadj
     row["adjoint"] = {"steps": nadj, "ms_per_step": round(adj_ms, 4), "ratio_adjoint_over_forward": adj_ms / ms,
@@ -429,8 +442,11 @@ def main():
     value = npart * args.steps / (fw["ms"] * 1e-3)
 
     # dominant kernel: the fused tile kernel (gather + push + deposit); its
-    # binding units are the VALU and the LDS pipe (not HBM), so the roofline
-    # is the vector-ALU one, with the HBM figures alongside
+    # binding units are the VALU, the LDS pipe and, in FP32 at order 3, the
+    # matrix cores (not HBM), so the roofline is the vector-ALU one, with the
+    # HBM figures alongside.  FP32 matrix products run at twice the vector rate
+    # (157 TFLOP/s): the fraction is of the vector peak, and with part of the
+    # flops on the matrix cores it is not bounded by one
     pk_ms, pk_n = fw["kernels"]["particles"]
     pk_avg = pk_ms / max(pk_n, 1)
     alg_bytes = particle_bytes(npart, tsize, w.species.w is not None) + field_bytes(ncell, tsize)
@@ -439,8 +455,9 @@ def main():
     hbm_gbs = alg_bytes / (pk_avg * 1e-3) / 1e9
     roofline = {"bound": "alu", "achieved": round(achieved_tf, 2), "peak": VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved_tf / VALU_PEAK_TFLOPS, 4), "traffic": MEASURED_TRAFFIC.get(w.name),
-                "kernel": tile_kernel_name(npart, ncell, tsize, g.order), "avg_ms": round(pk_avg, 4),
+                "kernel": tile_kernel_name(g, npart, w.dtype), "avg_ms": round(pk_avg, 4),
                 "alg_flops_per_particle": FLOPS_PER_PARTICLE[g.order],
+                "flops_on_matrix_cores": w.dtype == "f32" and g.order == 3,
                 "hbm_achieved_GBps": round(hbm_gbs, 1), "hbm_frac": round(hbm_gbs / HBM_PEAK_GBS, 4),
                 "alg_bytes_per_launch": int(alg_bytes),
                 "alg_bytes_per_particle": round(alg_bytes / npart, 2)}

@@ -196,3 +196,20 @@ def test_atomic_probe_library_loads():
     assert hasattr(lib, "picmb_run")
     ms, ops = C.c_double(), C.c_double()
     assert lib.picmb_run(99, 1, 1, 1, 1, C.byref(ms), C.byref(ops)) == -1   # bad mode: refused before any call
+
+
+@pytest.mark.parametrize("n, ppc, order, dtype, tile, kernel", [
+    ((256, 256, 256), 8, 3, "f32", (0, 0, 0), "k_particles_quads_dense"),
+    ((128, 128, 1024), 2, 3, "f32", (0, 0, 0), "k_particles_quads"),
+    ((512, 512, 512), 2, 3, "f32", (0, 0, 0), "k_particles_quads"),
+    ((256, 256, 256), 8, 3, "f64", (0, 0, 0), "k_particles_tile"),
+    ((32, 32, 32), 8, 1, "f64", (0, 0, 0), "k_particles_tile"),
+    ((192, 192, 192), 8, 3, "f32", (16, 8, 8), "k_particles_cells"),
+])
+def test_benchmark_names_the_kernel_that_a_workload_runs(n, ppc, order, dtype, tile, kernel):
+    import bench
+    g = wl.plasma_grid(n, order)
+    g.tile = tile
+    if tile[0]:
+        g.slack = 0
+    assert bench.tile_kernel_name(g, ppc * n[0] * n[1] * n[2], dtype) == kernel
