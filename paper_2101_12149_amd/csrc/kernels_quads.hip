@@ -1182,10 +1182,12 @@ static QuadPlan quad_plan(const TileGeo &tg, int64_t n)
         return QuadPlan{false, false, 0, 0};
     const int64_t ntiles = (int64_t)tg.nt[0] * tg.nt[1] * tg.nt[2];
     // With a CU for each tile a step takes the latency of its longest tile, and
-    // groups of one particle need more batches than a workgroup has waves
-    // (42 x 20 x 35 in 120 tiles, 1 per cell: 32.6 us a step on one
-    // particle per thread, 37.6 in groups; 16^3 in 64 tiles 30.5 / 26.1 us).
-    if (ntiles <= QD_CUS && cells > 512 / 64 * 16 && 2 * n < 3 * cells * ntiles)
+    // groups of one or two particles need more batches than a workgroup has
+    // waves.  One particle per thread / groups, us a step: 42 x 20 x 35 in 120
+    // tiles, 1 per cell 32.6 / 37.6, 2 per cell 35.5 / 38.1; 14 x 21 x 16 in 24
+    // tiles, 2 per cell 33.8 / 35.8, 4 per cell 42.8 / 36.4; 16^3 in 64 tiles, 1
+    // per cell 30.5 / 26.1.
+    if (ntiles <= QD_CUS && cells > 512 / 64 * 16 && 2 * n < 5 * cells * ntiles)
         return QuadPlan{false, false, 0, 0};
     // what a tile holds on average, with room for uneven ones
     const int64_t want = (n + ntiles - 1) / ntiles * 9 / 8 + 64;

@@ -843,7 +843,9 @@ def test_f32_order3_tile_step_on_large_tiles_matches_oracle(case):
 @pytest.mark.parametrize("case", [
     # columns as above
     ((16, 20, 35), (4, 5, 7), 1, 11000, 0, True, False, 3),     # few tiles, one particle per cell: one-pass kernel
-    ((16, 20, 35), (4, 5, 7), 1, 22000, 0, True, False, 3),     # two per cell: groups, all threads
+    ((16, 20, 35), (4, 5, 7), 1, 45000, 0, True, False, 3),     # four per cell: groups
+    ((16, 16, 16), (4, 4, 4), 1, 8200, 0, False, True, 3),      # few small tiles: groups, all threads
+    ((16, 16, 16), (8, 8, 8), 1, 11000, 0, True, False, 3),     # groups in the shared layout, constant pitches
     ((28, 28, 28), (4, 4, 4), 1, 22000, 0, False, False, 3),    # more tiles than CUs: fewest threads
     ((14, 21, 16), (7, 7, 4), 1, 56000, 0, True, False, 1),     # few tiles of more than a round: dense layout
     ((28, 28, 28), (4, 4, 4), 1, 660000, 0, False, False, 1),   # many such: rounds of the shared layout
@@ -853,7 +855,7 @@ def test_f32_order3_tile_step_over_tile_counts_matches_oracle(case):
     test_f32_order3_tile_step_matches_oracle(case)
 
 
-@pytest.mark.parametrize("npart", [8200, 28000])
+@pytest.mark.parametrize("npart", [8200, 11000, 28000])
 @pytest.mark.parametrize("axis", [0, 1, 2])
 def test_f32_order3_value_beyond_a_particles_window_is_not_read(axis, npart):
     """The matrix-core kernels read five nodes along a staggered axis, of which
@@ -885,6 +887,10 @@ def test_f32_order3_value_beyond_a_particles_window_is_not_read(axis, npart):
     back = torch.argsort(perm.cpu().long())
     assert max_rel(_cpu(gsp.u)[:, back.numpy()], osp.u) < 4e-6
     assert rel_l2(_cpu(gf.J), of.J) < 1e-5
+
+
+def test_f32_order3_groups_in_the_shared_layout_leave_corrupt_particles_out():
+    test_f32_order3_tile_step_leaves_corrupt_particles_out(11000)
 
 
 @pytest.mark.parametrize("ppc", [2, 8])
