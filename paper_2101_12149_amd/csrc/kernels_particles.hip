@@ -1755,6 +1755,7 @@ struct CellBox {
 };
 
 constexpr int OPS_MIN = 512;        // smallest segment tried as a box
+constexpr int64_t OPS_SMALL = 49152;   // particles of a small species
 constexpr int OPS_MAX_EXT = 480;    // cells per axis (the region walk takes rows of at most blockDim.x)
 constexpr int OPS_HEAD = 512;       // reduction scratch ahead of the regions, bytes
 static_assert((16 * 7 + 4) * (int)sizeof(int) <= OPS_HEAD, "box reduction scratch of 16 waves");
@@ -1865,9 +1866,10 @@ struct OpsThreads {
     static constexpr size_t gather_lds = sizeof(T) == 4 ? 80 * 1024 : 160 * 1024;
 };
 
-// Shortest segment that the gather halves to: below 512 particles a box pays
-// for the wide window in FP32 only (2.2 M listed cell by cell along x, 2 per
-// cell, at 512 / 256: FP32 737 / 486 us, FP64 811 / 1057 us).
+// Shortest segment that the gather halves a long run to: with the wide window in
+// FP32 below 512 particles, for lists whose rows are wider than a box (2.2 M cell
+// by cell along x, 2 per cell, at 512 / 256: FP32 737 / 486 us, FP64 1143 / 1057
+// us; 3.4 M by tiles, 6 per cell, drifted, FP32 350 / 370 us).
 template <typename T, int O>
 __device__ constexpr int gather_min()
 {
@@ -1921,7 +1923,7 @@ __global__ void __launch_bounds__(OpsThreads<T>::gather) k_gather_box(PConst<T> 
     T *sF = reinterpret_cast<T *>(smem_raw + OPS_HEAD);   // 6 * room values
     const int64_t base = (int64_t)blockIdx.x * chunk;
     const int64_t end = base + chunk < sp.n ? base + chunk : sp.n;
-    int len = chunk;
+    int len = chunk, misses = 0;
     for (int64_t s0 = base; s0 < end;) {
         int seg = (int)(end - s0 < len ? end - s0 : len);
         const CellBox b = segment_box(sp, pc.n, s0, seg, reinterpret_cast<int *>(smem_raw));
@@ -1929,18 +1931,20 @@ __global__ void __launch_bounds__(OpsThreads<T>::gather) k_gather_box(PConst<T> 
         size_t vol_box;
         const bool fits = b.any && box_region(b, halo, (size_t)room, ext, vol_box);
         if (b.any && !fits) {   // uniform: every thread has the same box
-            if (len > gather_min<T, O>()) {
+            if (len > (chunk > OPS_MIN ? gather_min<T, O>() : OPS_MIN)) {
                 len >>= 1;
                 continue;
             }
-            // A box not much too large: the rest of the run is mostly in the
-            // same order (cell by cell along x on a wide grid) and is gathered
-            // from global memory without barriers, 2.2 M particles at 2 per
-            // cell, FP64 1057 -> 811 us.  Particles in no order keep the
-            // barriers, as fewer waves at a time thrash the caches less
+            // The second box in turn that is not much too large (one may
+            // straddle two tiles): the rest of the run is mostly in the same
+            // order (cell by cell along x on a wide grid) and is gathered
+            // from global memory without barriers.  Particles in no order keep
+            // the barriers, as fewer waves at a time thrash the caches less
             // (2 M, FP64: 2.0 against 3.4 ms).
-            if (vol_box <= OPS_NEAR * (size_t)room)
+            if (vol_box <= OPS_NEAR * (size_t)room && ++misses == 2)
                 seg = (int)(end - s0);
+        } else {
+            misses = 0;
         }
         const int vol = fits ? ext[0] * ext[1] * ext[2] : 0;
         const int sf[3] = {1, ext[0], ext[0] * ext[1]};
@@ -3003,20 +3007,24 @@ hipError_t launch_particles_global(int order, const PConst<T> &pc, const PArr<T>
     return hipGetLastError();
 }
 
-// consecutive particles per workgroup of the box kernels: a tile's worth at
+// Consecutive particles per workgroup of the box kernels: a tile's worth at
 // 8 per cell, less on a small species so that there are two workgroups per CU.
-// Below 512 the boxes' halos cost more, so these are for species that would
-// leave a quarter of the CUs without a workgroup (order 3, binned, runs of 128
-// / 256 / 512: 32 K particles, FP32 gather 69 / 69 / 73 us, deposit drifted
-// from its tiles 96 / 93 / 191 us; 110 K, deposit 144 / 107 / 91 us).
+// Below 512 the boxes' halos cost more, the deposit's (whose values are all
+// flushed) more than the gather's, so these are for species that would leave
+// CUs without a workgroup (order 3, FP32, binned, runs of 128 / 256 / 512:
+// gather, 32 K, 8 per cell 69 / 69 / 73 us, 110 K 80 / 74 / 74 us; deposit, 41 K,
+// 1 per cell 104 / 84 / 89 us, 74 K, 8 per cell 144 / 108 / 92 us).
 static int ops_chunk(int64_t n)
 {
     int c = 4096;
     while (c > OPS_MIN && n < (int64_t)c * 512)
         c >>= 1;
-    while (c > 128 && n < (int64_t)c * 192)
-        c >>= 1;
     return c;
+}
+
+static int deposit_chunk(int64_t n)
+{
+    return n < OPS_SMALL ? 256 : ops_chunk(n);
 }
 
 // launch of a box kernel: particles and threads per workgroup, LDS bytes
@@ -3030,17 +3038,22 @@ static OpsPlan ops_plan(int chunk, int threads, size_t lds)
     return OpsPlan{chunk, chunk < threads ? chunk : threads, lds};
 }
 
-// The gather's runs: a CU takes as many as its share rounded up, and a shorter
-// run costs more per particle (its halo, GATHER_HALO particles' worth here) but
-// leaves less of the last round empty (2.2 M particles, 2 per cell, FP32: 2.15
-// runs of 4096 per CU 142 us, 8.6 of 1024 125 us).
+// The gather's runs in large species: a CU takes as many as its share rounded
+// up, and a shorter run costs more per particle (its halo, GATHER_HALO
+// particles' worth here) but leaves less of the last round empty (2.2 M
+// particles, 2 per cell, order 1, FP32: 2.15 runs of 4096 per CU 142 us, 8.6 of
+// 1024 125 us; 3.4 M, 6 per cell, order 3 427 / 370 us).  Dense first-order
+// species, whose boxes are cheap to stage, keep the long ones (2.3 M, 12 per
+// cell 107 / 115 us).
 constexpr int GATHER_HALO = 192, GATHER_CUS = 256;
 
-static int gather_chunk(int64_t n)
+static int gather_chunk(int64_t n, bool keep)
 {
+    if (n < 2 * OPS_SMALL)
+        return n < OPS_SMALL ? 128 : 256;
     int best = ops_chunk(n);
     int64_t least = INT64_MAX;
-    for (int c = best; c >= OPS_MIN; c >>= 1) {
+    for (int c = best; c >= OPS_MIN && !keep; c >>= 1) {
         const int64_t per = (int64_t)c * GATHER_CUS, t = (n + per - 1) / per * (c + GATHER_HALO);
         if (t < least) {
             least = t;
@@ -3056,6 +3069,7 @@ static hipError_t launch_gather_o(const PConst<T> &pc, const PArr<T> &sp, const 
 {
     static bool attr = false;
     allow_big_lds(&k_gather_box<T, O>, attr);
+    bool dense = false;
     if constexpr (O == 1) {
         // The window's 48 reads per particle come from the caches as fast as
         // a box can be staged, unless many particles share it.  A call, one
@@ -3063,14 +3077,14 @@ static hipError_t launch_gather_o(const PConst<T> &pc, const PArr<T> &sp, const 
         // 66.8 us, 262 K 74 / 71 us, 2 M 148 / 92 us; 2 per cell, 1 M 103 /
         // 93 us; FP64, 8 per cell, 512 K 86 / 107 us, 1.4 M 112 / 117 us, 2 M
         // 131 / 114 us; 2 per cell, 2.2 M, in no order 951 / 1187 us.
-        const bool dense = sp.n >= 4 * (int64_t)pc.n[0] * pc.n[1] * pc.n[2];
+        dense = sp.n >= 4 * (int64_t)pc.n[0] * pc.n[1] * pc.n[2];
         if (sizeof(T) == 4 ? sp.n < ((int64_t)1 << 17) : sp.n < ((int64_t)3 << 19) || !dense) {
             hipLaunchKernelGGL((k_gather<T, O>), dim3(nblk(sp.n, 256)), dim3(256), 0, st, pc, sp, f, Ep[0], Ep[1],
                                Ep[2], Bp[0], Bp[1], Bp[2], err);
             return hipGetLastError();
         }
     }
-    const OpsPlan P = ops_plan(gather_chunk(sp.n), OpsThreads<T>::gather, OpsThreads<T>::gather_lds);
+    const OpsPlan P = ops_plan(gather_chunk(sp.n, dense), OpsThreads<T>::gather, OpsThreads<T>::gather_lds);
     const int room = (int)((P.lds - OPS_HEAD) / (6 * sizeof(T)));
     hipLaunchKernelGGL((k_gather_box<T, O>), dim3(nblk(sp.n, P.chunk)), dim3(P.threads), P.lds, st, pc, sp, f, Ep[0],
                        Ep[1], Ep[2], Bp[0], Bp[1], Bp[2], P.chunk, room, err);
@@ -3102,14 +3116,16 @@ template <typename T, int O>
 static hipError_t launch_deposit_o(const PConst<T> &pc, const PArr<T> &before, const PArr<T> &after,
                                    const FieldPtrs<T> &f, int *err, hipStream_t st)
 {
-    // At first order 40 KB hold the box of a run of 256, which leaves four
-    // workgroups per CU; from 2^19 on a tile's worth per run saves more of the
-    // boxes' halos (binned, 8 per cell, 512 K 101 / 120 us, 884 K 127 / 122 us;
-    // 2 per cell, 524 K 102 / 95 us).  Below 49152 see k_deposit_box (64 K, 2
-    // per cell, drifted from its tiles: 75 us with boxes, 89 without).
+    // At first order 80 KB hold the box of a run of 512, also one that
+    // straddles two tiles, which leaves two workgroups per CU; from 2^19 on a
+    // tile's worth per run saves more of the boxes' halos.  A small species see
+    // k_deposit_box (64 K, 2 per cell, drifted from its tiles: 75 us with boxes,
+    // 89 without).  Runs of 256 in 40 KB / 512 in 80 KB / one workgroup per CU,
+    // 339 K at 2 per cell, hot: 163 / 98 / 110 us.
+    const bool few = before.n < OPS_SMALL;
     const OpsPlan P = O == 1 && before.n < ((int64_t)1 << 19)
-                          ? ops_plan(256, 256, 40 * 1024)
-                          : ops_plan(ops_chunk(before.n), OpsThreads<T>::deposit, 160 * 1024);
+                          ? (few ? ops_plan(256, 256, 40 * 1024) : ops_plan(512, 512, 80 * 1024))
+                          : ops_plan(deposit_chunk(before.n), OpsThreads<T>::deposit, 160 * 1024);
     const int room = (int)((P.lds - OPS_HEAD - 2 * (size_t)P.chunk) / (3 * sizeof(double)));
     auto launch = [&](auto *kernel, bool &attr) {
         allow_big_lds(kernel, attr);
@@ -3118,7 +3134,7 @@ static hipError_t launch_deposit_o(const PConst<T> &pc, const PArr<T> &before, c
     };
     static bool attr = false, attr_direct = false;
     if constexpr (O == 1) {
-        if (before.n < 49152) {
+        if (few) {
             launch(&k_deposit_box<T, O, true>, attr_direct);
             return hipGetLastError();
         }

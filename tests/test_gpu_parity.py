@@ -237,12 +237,12 @@ def test_separate_gather_and_deposit_on_boxes_match_oracle(order, dtype, layout)
 
 
 @pytest.mark.parametrize("order, dtype, n, grid, layout", [
-    (1, "f32", 60001, (32, 24, 40), "tiles"),        # deposit on boxes of runs of 256, gather per particle
+    (1, "f32", 60001, (32, 24, 40), "tiles"),        # deposit on boxes of runs of 512, gather per particle
     (1, "f64", 60001, (32, 24, 40), "scattered"),    # ... whose boxes do not fit
     (1, "f32", 140003, (32, 24, 40), "tiles"),       # gather on boxes too
     (1, "f64", 1600003, (64, 48, 40), "cells"),      # ... in FP64, runs of 2048
-    (3, "f32", 40009, (32, 24, 40), "scattered"),    # runs of 128
-    (3, "f64", 90001, (32, 24, 40), "tiles"),        # runs of 256
+    (3, "f32", 40009, (32, 24, 40), "scattered"),    # gather runs of 128, deposit 256
+    (3, "f64", 90001, (32, 24, 40), "tiles"),        # gather runs of 256, deposit 512
     (3, "f32", 600011, (240, 40, 32), "cells"),      # rows wider than a box: halved to 256
     (3, "f64", 600011, (240, 40, 32), "cells"),      # ... or the rest of the run per particle
 ])
