@@ -225,40 +225,46 @@ void region_extents(int order, TileGeo &tg)
 }
 
 // LDS layout of the one-pass tile kernel.  Lanes are consecutive cells along
-// x, then y, then z: with pitches that equal the tile's (or its negative)
-// modulo 32 words (rows of six interleaved field components, planes),
-// consecutive lanes fall on consecutive banks.  The rows of a current component
-// are too short for that on tiles of seven or eight cells; folded rows of 16
-// values do the same there (on narrower ones three rows share the banks and
-// folding only takes LDS).  What is left over holds the queue of cell-crossing
-// particles, up to 1024: two ints each, and their offsets too where that leaves
-// room for 256.  The layout with the most padding whose queue takes 256 is
-// chosen, else the bare regions (third order: by component).  FP64 order 3, particle kernel
-// with and without each: 128^3, 8 per cell (8 x 8 x 4 tiles) folded 12.5, rows
-// padded 13.3, bare 15.0 ms; 75 x 108 x 72, 6 per cell (5 x 6 x 8) folded, for
-// which nothing else is padded, 8.5, rows padded 7.3 ms; 108 x 110 x 57, 4 per
-// cell, hot (6 x 5 x 3) offsets in memory 3.10, in the queue 2.98 ms; 210 x 224
-// x 225, 1 per cell (7 x 8 x 5) bare interleaved rows 26.5, by component 25.6 ms.
+// x, then y, then z: with pitches that equal the tile's modulo 32 words (rows
+// of six interleaved field components, planes), consecutive lanes fall on
+// consecutive banks; with their negatives, which can be nearer, most do.  The
+// rows of a current component are too short for that on tiles of seven or eight
+// cells; folded rows of 16 values do the same there (on narrower ones three
+// rows share the banks and folding only takes LDS).  What is left over holds
+// the queue of cell-crossing particles, up to 1024: two ints each, and their
+// offsets too where there is room for that (an overflowing queue costs more
+// than offsets in memory).  The first layout of these whose
+// queue takes 256 is chosen: folded, rows and planes at the tile's pitch, at
+// either pitch, else the bare regions (third order: by component).
+// FP64 order 3, particle kernel with and without each: 128^3, 8 per cell (8 x 8
+// x 4 tiles) folded 12.5, padded 13.3, bare 15.0 ms; 91 x 195 x 180, 8 per cell,
+// hot (7 x 5 x 6) the tile's plane pitch 35.3, its negative 35.9 ms; 162 x 248 x
+// 222, 1 per cell (6 x 8 x 6) negative row pitch 12.0, bare 12.4 ms; 75 x 108 x
+// 72, 6 per cell (5 x 6 x 8) folded, for which nothing else is padded, 8.5,
+// padded 7.3 ms; 108 x 110 x 57, 4 per cell, hot (6 x 5 x 3) offsets in memory
+// 3.10, in the queue 2.98 ms; 20 x 14 x 28, 12 per cell, hot (5 x 7 x 7) 272 with
+// offsets in the queue 697, 1024 with theirs in memory 634 us; 210 x 224 x 225,
+// 1 per cell (7 x 8 x 5) bare interleaved rows 26.5, by component 25.6 ms.
 void tile_layout(GridInfo &gi, size_t limit)
 {
     TileGeo &tg = gi.tg;
     const int banks = 128 / (int)gi.tsize;   // values
-    auto pitch = [&](int p, int t) {
+    auto pitch = [&](int p, int t, bool negative) {
         t %= banks;
-        while (p % banks != t && p % banks != (banks - t) % banks)
+        while (p % banks != t && !(negative && p % banks == (banks - t) % banks))
             ++p;
         return p;
     };
     const bool folds = gi.order == 3 && (tg.t[0] == 7 || tg.t[0] == 8) && tg.rj[0] <= 16 && tg.rj[1] % 2 == 1;
     const bool small = tg.t[0] * tg.t[1] * tg.t[2] <= 64;
     const size_t most = small ? 256 : 1024;
-    for (int pad = folds ? 2 : 1; pad >= 0; --pad) {
-        tg.fold = pad == 2;
+    for (int pad = folds ? 3 : 2; pad >= 0; --pad) {
+        tg.fold = pad == 3;
         tg.jq = tg.fold ? 16 : tg.rj[0];
         if (pad > 0 || gi.order == 1) {
             tg.pm = tg.rf[0];
-            tg.pr = pad > 0 ? pitch(6 * tg.rf[0], tg.t[0]) : 6 * tg.rf[0];
-            tg.ps = pad > 0 ? pitch(tg.pr * tg.rf[1], tg.t[0] * tg.t[1]) : tg.pr * tg.rf[1];
+            tg.pr = pad > 0 ? pitch(6 * tg.rf[0], tg.t[0], pad == 1) : 6 * tg.rf[0];
+            tg.ps = pad > 0 ? pitch(tg.pr * tg.rf[1], tg.t[0] * tg.t[1], pad == 1) : tg.pr * tg.rf[1];
             tg.fvol = tg.ps * tg.rf[2];
         } else {
             tg.pr = tg.rf[0];
@@ -269,7 +275,7 @@ void tile_layout(GridInfo &gi, size_t limit)
         const size_t used = (((size_t)tg.fvol * gi.tsize + 15) & ~size_t(15)) +
                             tile_current_values(tg) * sizeof(double) + sizeof(int);
         const size_t left = limit > used ? limit - used : 0, full = 2 * sizeof(int) + 6 * gi.tsize;
-        tg.qoff = small || gi.order == 1 || pad == 0 || left / full >= 256;
+        tg.qoff = small || gi.order == 1 || pad == 0 || left / full >= most;
         const size_t room = left / (tg.qoff ? full : 2 * sizeof(int));
         tg.qcap = (int)(room < most ? room : most);
         if (tg.qcap >= 256)
