@@ -306,10 +306,20 @@ hipError_t launch_sum2(const double *in, double *out, hipStream_t st)
 // registers: SEG_PER, which share LDS as described below, or one, each on its
 // own, in species below SEG_MIN.  Those fit the caches and end with the
 // latency of a few dependent accesses (2^18 particles: 45 us a sort, 64 with
-// LDS; 6 M: 900 us, 750 with LDS).
+// LDS; 6 M: 900 us, 750 with LDS).  In a sparse species a segment touches more
+// cells, and LDS pays from a larger count on: SEG_SPARSE over the particles per
+// cell (pic_sort_tiles of a list cell by cell / drifted from its tiles, one per
+// thread against LDS: 2.4 M at 1 per cell 242 / 335 against 279 / 338 us, 2.2 M
+// at 2 per cell, FP64 296 / 417 against 310 / 432 us, 8 M at 1 per cell 723 /
+// 1058 against 696 / 912 us, 2.8 M at 2 per cell 274 / 369 against 255 / 326 us).
 static constexpr int SEG_PER = 4;
 static constexpr int SEG_T = 1024;
-static constexpr int64_t SEG_MIN = (int64_t)1 << 21;
+static constexpr int64_t SEG_MIN = (int64_t)1 << 21, SEG_SPARSE = (int64_t)5 << 20;
+
+static bool seg_staged(int64_t n, int64_t ncell)
+{
+    return n >= SEG_MIN && (double)n * (double)n >= (double)SEG_SPARSE * (double)ncell;
+}
 
 static unsigned seg_blocks(int64_t n, int per_block)
 {
@@ -658,7 +668,7 @@ hipError_t launch_bin_count(const PArr<T> &sp, const TileGeo &tg, int *counts, i
     if (sp.n == 0)
         return hipSuccess;
     const int n0 = tg.t[0] * tg.nt[0], n1 = tg.t[1] * tg.nt[1], n2 = tg.t[2] * tg.nt[2];
-    if (sp.n < SEG_MIN) {
+    if (!seg_staged(sp.n, (int64_t)n0 * n1 * n2)) {
         hipLaunchKernelGGL((k_bin_count<T, 1>), dim3(seg_blocks(sp.n, 256)), dim3(256), 0, st, sp, tg, n0, n1, n2,
                            counts, key, rank, err);
         return hipGetLastError();
@@ -1050,7 +1060,7 @@ hipError_t launch_scatter(const PArr<T> &in, const PArr<T> &out, const int *key,
                            offsets, slot_of, tile_start, old_start, tile_cells, perm);
         return hipGetLastError();
     }
-    if (in.n < SEG_MIN) {
+    if (!seg_staged(in.n, (int64_t)ntiles * tile_cells)) {
         hipLaunchKernelGGL((k_scatter<T, 1>), dim3(seg_blocks(in.n, 256)), dim3(256), 0, st, in, out, key, rank,
                            offsets, slot_of, tile_start, tile_cells, 0, perm);
         return hipGetLastError();

@@ -439,6 +439,13 @@ def test_sort_of_a_large_species_in_any_order(n, dtype, weights, order):
     assert bool((place[1:] > place[:-1]).all())
 
 
+@pytest.mark.parametrize("order", ["random", "loops", "drifted"])
+def test_sort_of_a_large_sparse_species_in_any_order(order):
+    """One particle per cell, which the sort takes one per thread up to a larger
+    count."""
+    test_sort_of_a_large_species_in_any_order((136, 128, 128), "f32", True, order)
+
+
 def test_sort_rejects_corrupt_state_without_touching_it():
     g = wl.plasma_grid((16, 16, 16), 3)
     sp = random_species(g, 1000, 62, dtype="f64")
