@@ -465,10 +465,10 @@ __device__ __attribute__((always_inline)) inline void deposit_still_shared(const
 // ---------------------------------------------------------------------------
 // The one-pass tile step.  In FP64 at third order the LDS pipe bounds it: a
 // wave's 384 field reads and some 200 atomics kept it 82 % busy, half of that
-// time on bank conflicts, against 37 % for the vector unit.  With the padded
-// and folded rows of tile_layout (which take 43 % of the conflict cycles away)
-// and 12 waves, 128^3 / 8 per cell went from 3.74 to 3.12 ms a step, 64^3 / 4
-// per cell from 288 to 249 us.  Staggered windows along y at five
+// time on bank conflicts, against 37 % for the vector unit (128^3, 8 waves).
+// With the padded and folded rows of tile_layout and 12 waves the LDS is busy 74
+// %, a third of it on conflicts, the vector unit 52 % (256^3): 128^3 / 8 per cell
+// went from 3.74 to 3.2 ms a step, 64^3 / 4 per cell from 288 to 249 us.  Staggered windows along y at five
 // fixed rows, which never conflict, read more than they saved (3.22 ms).
 // FOLD: the current rows are folded (a constant, as the index arithmetic costs
 // 1-2 % where they are not).
@@ -2915,8 +2915,8 @@ static hipError_t launch_tile_o(const PConst<T> &pc, const TileGeo &tg, const PA
 {
     static bool attr_cp = false, attr_cg = false;
     const unsigned ntiles = (unsigned)(tg.nt[0] * tg.nt[1] * tg.nt[2]);
-    // FP32 order 3 runs on the matrix cores (256^3, 8 per cell: 15.1 -> 12.8
-    // ms; 512^3, 2 per cell: 60.0 -> 44.4 ms) unless the tile is too large
+    // FP32 order 3 runs on the matrix cores (256^3, 8 per cell: 15.1 -> 12.5
+    // ms; 512^3, 2 per cell: 60.0 -> 43.2 ms) unless the tile is too large
     // for it.  There the per-cell deposit pays where cells hold many
     // particles, which share one row update per cell: 256^3, 8 per cell,
     // 21.2 -> 16.6 ms.  It loses at low densities (the laser box, 2 per

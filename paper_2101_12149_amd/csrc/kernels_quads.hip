@@ -25,12 +25,13 @@
 // that changes cells deposits the full window after the loop.
 //
 // Against one thread per particle (k_particles_tile; k_particles_cells from 6
-// per cell on), particle kernels per step: 256^3, 8 per cell 15.1 -> 12.8 ms;
-// 128 x 128 x 1024 laser box, 2 per cell 6.4 -> 5.0 ms; 512^3, 2 per cell, hot
-// 60 -> 44 ms; 128^3 in 4^3 tiles, 2 per cell 3.1 -> 1.1 ms.  The matrix core
-// and the vector unit take about half the time each of what is left of the
-// gather's and deposit's arithmetic; the LDS atomics of the deposit and the
-// latencies of the phases make up the rest.
+// per cell on), particle kernels per step: 256^3, 8 per cell 15.1 -> 12.5 ms;
+// 128 x 128 x 1024 laser box, 2 per cell, with a laser pulse 6.4 -> 4.9 ms;
+// 512^3, 2 per cell, hot 60 -> 43 ms; 128^3 in 4^3 tiles, 2 per cell 3.1 ->
+// 1.1 ms.  What is left is latency: at 256^3 (one workgroup of 16 waves on a
+// CU) the vector units are busy 58 % of the time, the LDS 52 %, the matrix cores
+// 12 %, in the laser box (two workgroups of 8) 69, 46 and 14 %; HBM is at 1.8
+// TB/s and 1.4 TB/s.
 #include <type_traits>
 
 #include "particle_common.hpp"
@@ -949,9 +950,10 @@ __device__ __attribute__((always_inline)) inline bool quad_tile(TileSpan &ts, Qu
 // gathers and moves up to QD_BATCH batches, keeping what their deposit needs
 // in registers; then the currents take the fields' place in LDS and the
 // batches are deposited.  Of the 148k clocks that a workgroup of the laser box
-// takes, staging is 15k, the lists 37k, the batches 36k, the deposit 22k, the
-// cell-changing particles 13k and the flush 10k: latencies in turn, which two
-// workgroups on a CU overlap.
+// took (clock counters between the phases, in a copy of the kernel), staging was
+// 15k, the lists 37k, the batches 36k, the deposit 22k, the cell-changing
+// particles 13k and the flush 10k: latencies in turn, which two workgroups on a
+// CU overlap.
 template <bool G, int PRC, int PSC, int RFX>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k_particles_quads(QuadArgs)
 {
